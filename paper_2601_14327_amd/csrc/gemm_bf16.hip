@@ -37,25 +37,6 @@
 namespace laep {
 namespace {
 
-// fourth word of a raw buffer resource: 32-bit data format, no swizzle
-constexpr int kBufferFlags = 0x00020000;
-
-// Global -> LDS copy of NC 16-byte chunks per thread through buffer loads
-// with the LDS flag: chunk i of this thread is at byte voff[i] + soff of the
-// operand's buffer.  (The global-segment form of the same copy makes the
-// compiler drain every outstanding LDS read, lgkmcnt(0), before each fragment
-// use in the loop; with the buffer form it counts them in order.)  A device
-// function, not a lambda: the host pass of a kernel must not see the LDS-DMA
-// builtin inside a lambda, or the kernel's launch stub is dropped.
-template <int NC, int NT>
-__device__ __forceinline__ void dma_chunks(char* dst, __amdgpu_buffer_rsrc_t rsrc,
-                                           const uint32_t* voff, int soff, int wave) {
-#pragma unroll
-  for (int i = 0; i < NC; ++i)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)(dst + (i * NT + wave * 64) * 16),
-                                             16, voff[i], soff, 0, 0);
-}
-
 // Tile of the XCD-contiguous schedule owned by this workgroup, or -1.
 __device__ __forceinline__ int xcd_tile(const GemmParams& p) {
   const int n_valid = (*p.n_entries) * p.tiles_per_entry;
@@ -854,6 +835,9 @@ hipError_t launch_ffn_fwd_products(const void* x_perm, const void* w_gu, const v
                                    int d, int f, int64_t R, void* y_perm, void* act_save,
                                    bf16_t* H, void* ws, hipStream_t s, const int32_t* row_src,
                                    int slots_k, const float* gate, void* out_tok) {
+  if (const int bm = small_fwd_bm(R, E, d, f))
+    return launch_ffn_fwd_small(bm, x_perm, w_gu, w_d, offsets, expert_map, E, d, f, R, y_perm,
+                                act_save, H, s, row_src, slots_k, gate, out_tok);
   const int nt_gu = ceil_div(f, kFwdBN / 2), nt_d = ceil_div(d, kFwdBN);
   const int max_gu = fwd_list_max(R, E, nt_gu), max_d = fwd_list_max(R, E, nt_d);
   char* tables = static_cast<char*>(ws) + align_up((size_t)R * f * 2, 256);

@@ -61,8 +61,6 @@ constexpr int kRingHalf = 256 * kRingRowB;   // one operand's k-step: 32 KB
 constexpr int kRingSlots = 5;
 constexpr int kTrRowB = 512;                 // K-strided half: bytes per k-row (256 features)
 constexpr int kTrCpr = kTrRowB / 16;         // 16-byte chunks per k-row
-// fourth word of a raw buffer resource: 32-bit data format, no swizzle
-constexpr int kBufferFlags = 0x00020000;
 
 // LDS slot q of a TR tile -> (k-row, element column within the tile)
 __device__ __forceinline__ void tr_slot(int q, int cpr, int& r, int& col) {

@@ -98,6 +98,28 @@ __device__ __forceinline__ void wait_vmcnt_lgkm0() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
 }
 
+// cache policy of a copy whose data is read once (non-temporal)
+constexpr int kDmaStream = 2;
+
+// fourth word of a raw buffer resource: 32-bit data format, no swizzle
+constexpr int kBufferFlags = 0x00020000;
+
+// Global -> LDS copy of NC 16-byte chunks per thread through buffer loads
+// with the LDS flag: chunk i of this thread is at byte voff[i] + soff of the
+// operand's buffer.  (The global-segment form of the same copy makes the
+// compiler drain every outstanding LDS read, lgkmcnt(0), before each fragment
+// use in the loop; with the buffer form it counts them in order.)  A device
+// function, not a lambda: the host pass of a kernel must not see the LDS-DMA
+// builtin inside a lambda, or the kernel's launch stub is dropped.
+template <int NC, int NT, int POLICY = 0>
+__device__ __forceinline__ void dma_chunks(char* dst, __amdgpu_buffer_rsrc_t rsrc,
+                                           const uint32_t* voff, int soff, int wave) {
+#pragma unroll
+  for (int i = 0; i < NC; ++i)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)(dst + (i * NT + wave * 64) * 16),
+                                             16, voff[i], soff, 0, POLICY);
+}
+
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
 inline int round8(int v) { return (v + 7) & ~7; }
 

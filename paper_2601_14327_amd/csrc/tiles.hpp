@@ -184,6 +184,70 @@ __global__ __launch_bounds__(kTableThreads) void build_tile_lists_kernel(
   }
 }
 
+struct FoundTile : TileEntry {
+  int expert_rows;
+};
+
+// The tile of this workgroup, found from the expert offsets (no list): tiles
+// of BM rows x n_tiles column blocks, experts in order, within an expert the
+// row tiles of a column block innermost (they share its weights); te also
+// says how many rows the expert has in all.  Each XCD
+// takes a contiguous range (block i runs on XCD i % 8).  256 threads, one per
+// expert; scratch: LDS, free again on return.  False: no tile.
+__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets,
+                                          const int32_t* __restrict__ expert_map, int E, int BM,
+                                          int n_tiles, char* scratch, FoundTile& te) {
+  int* const s_wave = reinterpret_cast<int*>(scratch);
+  volatile int* const s_te = reinterpret_cast<int*>(scratch) + 4;
+  const int e = threadIdx.x, lane = e & 63, wave = e >> 6;
+  int row0 = 0, rows = 0, phys = -1;
+  if (e < E) {
+    row0 = offsets[e];
+    rows = offsets[e + 1] - row0;
+    phys = expert_map ? expert_map[e] : e;
+  }
+  const int mt = phys >= 0 && rows > 0 ? (rows + BM - 1) / BM : 0;
+  const int cnt = mt * n_tiles;
+  int inc = cnt;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int n = __shfl_up(inc, off, 64);
+    if (lane >= off) inc += n;
+  }
+  if (lane == 63) s_wave[wave] = inc;
+  __syncthreads();
+  int total = 0, before = 0;
+#pragma unroll
+  for (int w = 0; w < kTableThreads / 64; ++w) {
+    const int n = s_wave[w];
+    before += w < wave ? n : 0;
+    total += n;
+  }
+  const int per = (total + 7) >> 3;
+  const int slot = blockIdx.x >> 3;
+  const int L = (int)(blockIdx.x & 7) * per + slot;
+  if (slot >= per || L >= total) return false;  // (uniform)
+  const int i = L - (before + inc - cnt);
+  if (i >= 0 && i < cnt) {  // one thread: its expert holds tile L
+    const int n = i / mt, m = i % mt;
+    s_te[0] = row0 + m * BM;
+    s_te[1] = min(BM, rows - m * BM);
+    s_te[2] = e;
+    s_te[3] = phys;
+    s_te[4] = n;
+    s_te[5] = rows;
+  }
+  __syncthreads();
+  te.row0 = __builtin_amdgcn_readfirstlane(s_te[0]);
+  te.rows = __builtin_amdgcn_readfirstlane(s_te[1]);
+  te.expert = __builtin_amdgcn_readfirstlane(s_te[2]);
+  te.phys = __builtin_amdgcn_readfirstlane(s_te[3]);
+  te.nt = __builtin_amdgcn_readfirstlane(s_te[4]);
+  te.expert_rows = __builtin_amdgcn_readfirstlane(s_te[5]);
+  __syncthreads();  // read by every thread: the scratch is free
+  return true;
+}
+
 struct TableWs {
   int* n_entries;
   TileEntry* table;
