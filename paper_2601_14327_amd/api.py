@@ -92,7 +92,8 @@ def moe_route_bwd(dgate: torch.Tensor, topk_idx: torch.Tensor, topk_gate: torch.
     E, d = w_router.shape
     dev = x.device
     if data:
-        dx = torch.zeros_like(x) if dx is None else dx
+        if dx is None:   # overwritten whole unless accumulated onto
+            dx = torch.zeros_like(x) if accumulate_dx else torch.empty_like(x)
     else:
         dx = None
     if weights:

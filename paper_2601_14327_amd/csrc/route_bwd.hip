@@ -18,55 +18,90 @@ namespace {
 
 constexpr int kDlThreads = 256;
 
-// One thread per token.  renorm: dl_slot[t, j] = g_j (dg_j - sum_i g_i dg_i)
-// (0 for unrouted slots).  Full softmax: dl_full[t, e] = p_e (q_e - sum_j g_j dg_j)
-// over alive e, p = softmax of the alive logits, q_e = dg_j at e = idx[t, j].
-// dlogits (optional) gets the dense [T, E] gradient in both cases.
+// Renormalised gates, one thread per token: dl_slot[t, j] =
+// g_j (dg_j - sum_i g_i dg_i) (0 for unrouted slots).  dlogits (optional)
+// gets the dense [T, E] gradient.
 __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_kernel(
     const float* __restrict__ dgate, const int32_t* __restrict__ idx,
-    const float* __restrict__ gate, const float* __restrict__ logits,
-    const uint8_t* __restrict__ alive, int T, int E, int k, int renorm,
-    float* __restrict__ dl_out, float* __restrict__ dlogits) {
+    const float* __restrict__ gate, int T, int E, int k, float* __restrict__ dl_out,
+    float* __restrict__ dlogits) {
   const int t = blockIdx.x * kDlThreads + threadIdx.x;
   if (t >= T) return;
   const size_t s0 = (size_t)t * k;
   float s = 0.0f;
   for (int j = 0; j < k; ++j)
     if (idx[s0 + j] >= 0) s += gate[s0 + j] * dgate[s0 + j];
-  if (renorm) {
-    if (dlogits)
-      for (int e = 0; e < E; ++e) dlogits[(size_t)t * E + e] = 0.0f;
-    for (int j = 0; j < k; ++j) {
-      const int e = idx[s0 + j];
-      const float v = e >= 0 ? gate[s0 + j] * (dgate[s0 + j] - s) : 0.0f;
-      dl_out[s0 + j] = v;
-      if (dlogits && e >= 0) dlogits[(size_t)t * E + e] = v;
-    }
-  } else {
-    const float* l = logits + (size_t)t * E;
-    float m = -INFINITY;
-    for (int e = 0; e < E; ++e)
-      if (alive == nullptr || alive[e]) m = fmaxf(m, l[e]);
-    float z = 0.0f;
-    for (int e = 0; e < E; ++e)
-      if (alive == nullptr || alive[e]) z += __expf(l[e] - m);
-    const float inv = z > 0.0f ? 1.0f / z : 0.0f;
-    for (int e = 0; e < E; ++e) {
-      float q = 0.0f;
-      for (int j = 0; j < k; ++j)
-        if (idx[s0 + j] == e) q = dgate[s0 + j];
-      const bool a = alive == nullptr || alive[e];
-      const float v = a ? __expf(l[e] - m) * inv * (q - s) : 0.0f;
-      dl_out[(size_t)t * E + e] = v;
-      if (dlogits) dlogits[(size_t)t * E + e] = v;
-    }
+  if (dlogits)
+    for (int e = 0; e < E; ++e) dlogits[(size_t)t * E + e] = 0.0f;
+  for (int j = 0; j < k; ++j) {
+    const int e = idx[s0 + j];
+    const float v = e >= 0 ? gate[s0 + j] * (dgate[s0 + j] - s) : 0.0f;
+    dl_out[s0 + j] = v;
+    if (dlogits && e >= 0) dlogits[(size_t)t * E + e] = v;
   }
 }
 
-// dx[t] (+)= sum over slots of w * W_r[row]: `slots` per token, row ids from
-// `ids` ([T, slots], -1 = none) or the slot number itself when ids == NULL,
-// weights dl [T, slots].  One wave per token (its ids and weights are
-// wave-uniform loads); each lane owns the 8-column vectors lane, lane + 64, ...
+// Full-softmax gates: dl_full[t, e] = p_e (q_e - sum_j g_j dg_j) over alive e,
+// p = softmax of the alive logits, q_e = dg_j at e = idx[t, j].  One wave per
+// token, lane l owning experts l, l + 64, ...: the logits are read and dl
+// written in whole lines (one thread per token walked its row alone, every
+// load touching 64 lines: 103 us at 4096 tokens over 128 experts).
+__global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
+    const float* __restrict__ dgate, const int32_t* __restrict__ idx,
+    const float* __restrict__ gate, const float* __restrict__ logits,
+    const uint8_t* __restrict__ alive, int T, int E, int k, float* __restrict__ dl_out,
+    float* __restrict__ dlogits) {
+  const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * (kDlThreads / 64) +
+                                               (int)(threadIdx.x >> 6));
+  if (t >= T) return;
+  const int lane = threadIdx.x & 63;
+  const size_t s0 = (size_t)t * k;
+  float s = 0.0f;
+  for (int j = lane; j < k; j += 64)
+    if (idx[s0 + j] >= 0) s += gate[s0 + j] * dgate[s0 + j];
+  s = wave_sum(s);
+  constexpr int EPL = 4;  // at most 256 experts
+  float l[EPL], q[EPL];
+  bool a[EPL];
+  float m = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    const int e = lane + 64 * u;
+    a[u] = e < E && (alive == nullptr || alive[e]);
+    l[u] = a[u] ? logits[(size_t)t * E + e] : -INFINITY;
+    q[u] = 0.0f;
+    m = fmaxf(m, l[u]);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
+  for (int j = 0; j < k; ++j) {  // (uniform loads)
+    const int ej = idx[s0 + j];
+    const float dg = dgate[s0 + j];
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) q[u] = ej == lane + 64 * u ? dg : q[u];
+  }
+  float z = 0.0f;
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    l[u] = a[u] ? __expf(l[u] - m) : 0.0f;
+    z += l[u];
+  }
+  z = wave_sum(z);
+  const float inv = z > 0.0f ? 1.0f / z : 0.0f;
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    const int e = lane + 64 * u;
+    if (e >= E) continue;
+    const float v = a[u] ? l[u] * inv * (q[u] - s) : 0.0f;
+    dl_out[(size_t)t * E + e] = v;
+    if (dlogits) dlogits[(size_t)t * E + e] = v;
+  }
+}
+
+// Renormalised gates: dx[t] (+)= sum over slots of w * W_r[row], row ids from
+// `ids` ([T, slots], -1 = none), weights dl [T, slots].  One wave per token (its
+// ids and weights are wave-uniform loads); each lane owns the 8-column vectors
+// lane, lane + 64, ...
 template <typename T>
 __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
     const T* __restrict__ w_router, const int32_t* __restrict__ ids,
@@ -85,8 +120,7 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
 #pragma unroll
       for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
     }
-    // slot order, in groups of 8 whose row loads are all issued before the
-    // sums; for full-softmax gates (ids == NULL) every expert is a slot
+    // slot order, in groups of 8 whose row loads are all issued before the sums
     float sum[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) sum[q] = 0.0f;
@@ -99,7 +133,7 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
         r[u] = -1;
         w[u] = 0.0f;
         if (s < slots) {
-          r[u] = ids ? ids[o + s] : s;
+          r[u] = ids[o + s];
           w[u] = dl[o + s];
         }
         if (w[u] == 0.0f) r[u] = -1;
@@ -127,75 +161,196 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
   }
 }
 
-// Full-softmax gates: dW_r[e, c0 + 0..255] and db[e] over every token t with
-// weight dl[t * E + e].  Workgroup (e, column chunk); 8 row lanes x 32 vector
-// lanes.  Row lane rl takes tokens rl, rl + 8, ...; the 8 partial sums are
-// then added in lane order through LDS.
-template <typename T>
-__global__ __launch_bounds__(256) void route_bwd_dw_kernel(
-    const T* __restrict__ x, const float* __restrict__ dl, int n_tok, int E, int d,
+// Dense products of the full-softmax gates (every alive expert carries a
+// gradient), on the fp32 matrix cores: dl stays fp32, and x and W_r are
+// widened exactly, so a product and its sum are fp32 as in a plain loop.
+//   kDx:  dx[t, c] (+)= sum_e dl[t, e] W_r[e, c]        (K = E)
+//   kDw:  part[s][e, c] = sum_{t in split s} dl[t, e] x[t, c], and the
+//         split's bias sums                             (K = T / splits)
+// 64 x 128 output tiles, 4 waves of 32 x 64 (v_mfma_f32_32x32x2_f32, operands
+// swapped: a lane owns one row and 4 consecutive columns per register quad),
+// 32 k at a time through LDS as [k][row], [k][column], the next 32 loaded into
+// registers beside the MFMAs.  dW_r has only E x d outputs, so its tokens are
+// split over enough workgroups to fill the chip twice and the partial tiles
+// summed in order by a second kernel.  (Before: one wave per token walking all
+// E rows of W_r for dx, one workgroup per (expert, 256 columns) reading all of
+// x, E times in all, for dW_r: 74 + 198 us at 4096 tokens, 128 experts, d 1024;
+// now 17 + 18 + 4 with the
+// sum of the partial tiles.)
+enum { kDx = 0, kDw = 1 };
+constexpr int kDenseBM = 64, kDenseBN = 128, kDenseKC = 32;
+
+template <typename T> struct Wide8;  // 8 consecutive elements -> fp32
+template <> struct Wide8<bf16_t> {
+  u32x4_t r;
+  __device__ __forceinline__ void zero() { r = u32x4_t{0u, 0u, 0u, 0u}; }
+  __device__ __forceinline__ void load(const bf16_t* p) {
+    r = *reinterpret_cast<const u32x4_t*>(p);
+  }
+  __device__ __forceinline__ void put(float* d) const {
+    *reinterpret_cast<f32x4_t*>(d) = f32x4_t{lo_bf16(r[0]), hi_bf16(r[0]), lo_bf16(r[1]), hi_bf16(r[1])};
+    *reinterpret_cast<f32x4_t*>(d + 4) = f32x4_t{lo_bf16(r[2]), hi_bf16(r[2]), lo_bf16(r[3]), hi_bf16(r[3])};
+  }
+};
+template <> struct Wide8<float> {
+  f32x4_t a, b;
+  __device__ __forceinline__ void zero() { a = b = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ void load(const float* p) {
+    a = *reinterpret_cast<const f32x4_t*>(p);
+    b = *reinterpret_cast<const f32x4_t*>(p + 4);
+  }
+  __device__ __forceinline__ void put(float* d) const {
+    *reinterpret_cast<f32x4_t*>(d) = a;
+    *reinterpret_cast<f32x4_t*>(d + 4) = b;
+  }
+};
+
+// Mrows: rows of the output (tokens for kDx, experts for kDw); K: the
+// reduction length; k_per: its length per split (a multiple of 32).
+template <typename T, int MODE>
+__global__ __launch_bounds__(256) void route_bwd_dense_kernel(
+    const float* __restrict__ dl, const T* __restrict__ B, const uint8_t* __restrict__ alive,
+    int Mrows, int K, int k_per, int E, int d, int accumulate, T* __restrict__ dx, float* __restrict__ part,
+    float* __restrict__ part_b) {
+  constexpr int BM = kDenseBM, BN = kDenseBN, KC = kDenseKC;
+  constexpr int LDA = BM + 33, LDB = BN + 4;  // LDA odd: transposed writes spread over the banks
+  __shared__ float sA[KC * LDA];
+  __shared__ __attribute__((aligned(16))) float sB[KC * LDB];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const int k0 = blockIdx.z * k_per, k1 = min(K, k0 + k_per);
+
+  float ra[BM * KC / 256];
+  Wide8<T> rb[KC * BN / 8 / 256];
+  auto load = [&](int kb) {
+#pragma unroll
+    for (int i = 0; i < BM * KC / 256; ++i) {
+      const int q = i * 256 + tid;
+      // kDx: dl rows are tokens, k contiguous; kDw: dl rows are k, experts contiguous
+      const int m = m0 + (MODE == kDx ? q / KC : q % BM);
+      const int kk = kb + (MODE == kDx ? q % KC : q / BM);
+      const bool ok = m < Mrows && kk < k1;
+      const size_t at = MODE == kDx ? (size_t)m * E + kk : (size_t)kk * E + m;
+      ra[i] = ok ? dl[at] : 0.0f;
+    }
+#pragma unroll
+    for (int i = 0; i < KC * BN / 8 / 256; ++i) {
+      const int q = i * 256 + tid;
+      const int kk = kb + q / (BN / 8), c = n0 + (q % (BN / 8)) * 8;
+      // kDx: a pruned expert's row of W_r is not read (its dl is 0, its weights anything)
+      const bool row_ok = kk < k1 && (MODE == kDw || alive == nullptr || alive[kk] != 0);
+      if (row_ok && c < d) rb[i].load(B + (size_t)kk * d + c);
+      else rb[i].zero();
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int i = 0; i < BM * KC / 256; ++i) {
+      const int q = i * 256 + tid;
+      if (MODE == kDx) sA[(q % KC) * LDA + q / KC] = ra[i];
+      else sA[(q / BM) * LDA + q % BM] = ra[i];
+    }
+#pragma unroll
+    for (int i = 0; i < KC * BN / 8 / 256; ++i) {
+      const int q = i * 256 + tid;
+      rb[i].put(sB + (q / (BN / 8)) * LDB + (q % (BN / 8)) * 8);
+    }
+  };
+  f32x16_t acc[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+  const bool sums_bias = MODE == kDw && part_b != nullptr && blockIdx.y == 0 && tid < BM;
+  float bias = 0.0f;
+
+  const int lr = lane & 31, h = lane >> 5;
+  if (k0 < k1) load(k0);
+  for (int kb = k0; kb < k1; kb += KC) {
+    store();
+    __syncthreads();
+    if (kb + KC < k1) load(kb + KC);
+#pragma unroll
+    for (int s = 0; s < KC / 2; ++s) {
+      const float a = sA[(2 * s + h) * LDA + wm * 32 + lr];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float b = sB[(2 * s + h) * LDB + wn * 64 + j * 32 + lr];
+        acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, acc[j], 0, 0, 0);
+      }
+    }
+    if (sums_bias)
+#pragma unroll
+      for (int kk = 0; kk < KC; ++kk) bias += sA[kk * LDA + tid];
+    __syncthreads();
+  }
+
+  const int row = m0 + wm * 32 + lr;
+  if (row < Mrows) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int c = n0 + wn * 64 + j * 32 + q * 8 + h * 4;
+        if (c >= d) continue;
+        f32x4_t v = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+        if constexpr (MODE == kDw) {
+          *reinterpret_cast<f32x4_t*>(part + ((size_t)blockIdx.z * Mrows + row) * d + c) = v;
+        } else if constexpr (sizeof(T) == 4) {
+          f32x4_t* p = reinterpret_cast<f32x4_t*>(dx + (size_t)row * d + c);
+          if (accumulate) v = *p + v;
+          *p = v;
+        } else {
+          u32x2_t* p = reinterpret_cast<u32x2_t*>(dx + (size_t)row * d + c);
+          if (accumulate) {
+            const u32x2_t o = *p;
+            v = f32x4_t{lo_bf16(o[0]), hi_bf16(o[0]), lo_bf16(o[1]), hi_bf16(o[1])} + v;
+          }
+          *p = u32x2_t{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        }
+      }
+  }
+  if (sums_bias && m0 + tid < Mrows) part_b[(size_t)blockIdx.z * Mrows + m0 + tid] = bias;
+}
+
+// dW_r = sum of the splits' partial tiles in split order, db likewise.  One
+// output per thread: the E x d outputs are few, so wider vectors would leave
+// the chip short of loads in flight.
+__global__ __launch_bounds__(256) void route_bwd_dense_reduce_kernel(
+    const float* __restrict__ part, const float* __restrict__ part_b, int splits, int E, int d,
     float* __restrict__ dw, float* __restrict__ db) {
-  __shared__ float s_part[8][32 * 8 + 4];
-  __shared__ float s_bias[8];
-  const int e = blockIdx.x;
-  const int chunk = blockIdx.y;
-  const int rl = threadIdx.x >> 5, vl = threadIdx.x & 31;
-  const int v = chunk * 32 + vl;              // 8-column vector index
-  const bool col_ok = v * 8 < d;
-  const int r0 = 0, r1 = n_tok;
-  float acc[8], bsum = 0.0f;
+  const size_t n = (size_t)E * d;
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  auto sum = [&](const float* p, size_t stride) {
+    float acc = 0.0f;
+    for (int s0 = 0; s0 < splits; s0 += 16) {
+      float v[16];
 #pragma unroll
-  for (int q = 0; q < 8; ++q) acc[q] = 0.0f;
-  // eight rows in flight per thread
-  for (int r = r0 + rl; r < r1; r += 64) {
-    int tok[8];
-    float w[8];
-    float val[8][8];
+      for (int u = 0; u < 16; ++u) v[u] = s0 + u < splits ? p[(s0 + u) * stride] : 0.0f;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int rr = r + 8 * u;
-      tok[u] = -1;
-      w[u] = 0.0f;
-      if (rr < r1) {
-        tok[u] = rr;
-        w[u] = dl[(size_t)rr * E + e];
-      }
+      for (int u = 0; u < 16; ++u) acc += v[u];
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (tok[u] >= 0 && col_ok) {
-        Elem<T>::load8(x + (size_t)tok[u] * d + (size_t)v * 8, val[u]);
-      } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) val[u][q] = 0.0f;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      bsum += w[u];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) acc[q] += w[u] * val[u][q];
-    }
-  }
-#pragma unroll
-  for (int q = 0; q < 8; ++q) s_part[rl][vl * 8 + q] = acc[q];
-  if (vl == 0) s_bias[rl] = bsum;
-  __syncthreads();
-  if (rl == 0 && col_ok) {
-    float out[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      float tsum = 0.0f;
-      for (int j = 0; j < 8; ++j) tsum += s_part[j][vl * 8 + q];
-      out[q] = tsum;
-    }
-    Elem<float>::store8(dw + (size_t)e * d + (size_t)v * 8, out);
-  }
-  if (db != nullptr && chunk == 0 && threadIdx.x == 0) {
-    float tsum = 0.0f;
-    for (int j = 0; j < 8; ++j) tsum += s_bias[j];
-    db[e] = tsum;
-  }
+    return acc;
+  };
+  if (i < n) dw[i] = sum(part + i, n);
+  if (db != nullptr && i < (size_t)E) db[i] = sum(part_b + i, E);
+}
+
+// Token splits of the dense dW_r: enough workgroups to fill the chip twice,
+// each with at least two 32-token steps.
+struct DenseSplit {
+  int n, per;
+};
+inline DenseSplit dense_split(int T, int E, int d) {
+  int tiles = ((E + kDenseBM - 1) / kDenseBM) * ((d + kDenseBN - 1) / kDenseBN);
+  if (tiles < 1) tiles = 1;
+  int n = (512 + tiles - 1) / tiles;
+  const int most = (T + 2 * kDenseKC - 1) / (2 * kDenseKC);
+  if (n > most) n = most;
+  if (n < 1) n = 1;
+  const int per = ((T + n - 1) / n + kDenseKC - 1) / kDenseKC * kDenseKC;
+  return {per > 0 ? (T + per - 1) / per : 0, per};
 }
 
 // Renormalised gates, weight gradient in two deterministic passes.
@@ -309,17 +464,75 @@ __global__ void fill_zero_kernel(float* __restrict__ p, size_t n) {
 
 }  // namespace
 
-// ws: dl, then (renormalised gates) the segment table, partial rows and sums.
-// The segment partials need d; the workspace query has none, so the partial
-// area is sized for the largest d_model the caller passes (d_model is an
-// argument of moe_workspace_bytes for the backward calls).
+// ws: dl; then, for renormalised gates, the segment table, partial rows and
+// sums; for full-softmax gates the splits' partial tiles and sums.
 inline int seg_max(int T, int k, int E) { return (int)(((int64_t)T * k + kSegRows - 1) / kSegRows) + E; }
 
 size_t route_bwd_ws_bytes(int T, int k, int E, int d) {
   const int m = seg_max(T, k, E);
-  return align_up((size_t)T * (k > E ? k : E) * sizeof(float), 256) + table_bytes(m) +
-         align_up((size_t)m * d * sizeof(float), 256) + align_up((size_t)m * sizeof(float), 256);
+  const size_t seg = table_bytes(m) + align_up((size_t)m * d * sizeof(float), 256) +
+                     align_up((size_t)m * sizeof(float), 256);
+  const size_t n = dense_split(T, E, d).n;
+  const size_t dense = align_up(n * E * d * sizeof(float), 256) + align_up(n * E * sizeof(float), 256);
+  return align_up((size_t)T * (k > E ? k : E) * sizeof(float), 256) + (seg > dense ? seg : dense);
 }
+
+namespace {
+
+template <typename T>
+hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const float* gate,
+                              const float* logits, const uint8_t* alive, const T* x,
+                              const T* w_router, const int32_t* offsets, const int32_t* row_src,
+                              int T_, int d, int E, int k, int renorm, float* dlogits,
+                              float* dw_router, float* dbias, T* dx, int accumulate_dx, void* ws,
+                              hipStream_t s) {
+  float* dl = static_cast<float*>(ws);
+  char* base = static_cast<char*>(ws) + align_up((size_t)T_ * (k > E ? k : E) * sizeof(float), 256);
+  if (!renorm) {
+    hipLaunchKernelGGL(route_bwd_dl_full_kernel, dim3((T_ + 3) / 4), dim3(kDlThreads), 0, s, dgate,
+                       idx, gate, logits, alive, T_, E, k, dl, dlogits);
+    const unsigned gn = (unsigned)((d + kDenseBN - 1) / kDenseBN);
+    if (dx)
+      hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDx>),
+                         dim3((unsigned)((T_ + kDenseBM - 1) / kDenseBM), gn), dim3(256), 0, s, dl,
+                         w_router, alive, T_, E, E, E, d, accumulate_dx, dx, nullptr, nullptr);
+    if (dw_router) {
+      const DenseSplit sp = dense_split(T_, E, d);
+      float* part = reinterpret_cast<float*>(base);
+      float* part_b = reinterpret_cast<float*>(base + align_up((size_t)sp.n * E * d * sizeof(float), 256));
+      hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDw>),
+                         dim3((unsigned)((E + kDenseBM - 1) / kDenseBM), gn, (unsigned)sp.n),
+                         dim3(256), 0, s, dl, x, nullptr, E, T_, sp.per, E, d, 0, static_cast<T*>(nullptr),
+                         part, dbias ? part_b : nullptr);
+      const size_t n = (size_t)E * d;  // >= E
+      hipLaunchKernelGGL(route_bwd_dense_reduce_kernel, dim3((unsigned)((n + 255) / 256)),
+                         dim3(256), 0, s, part, part_b, sp.n, E, d, dw_router, dbias);
+    }
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(route_bwd_dl_kernel, dim3((T_ + kDlThreads - 1) / kDlThreads),
+                     dim3(kDlThreads), 0, s, dgate, idx, gate, T_, E, k, dl, dlogits);
+  if (dx)
+    hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,
+                       w_router, idx, dl, T_, k, d, accumulate_dx, dx);
+  if (dw_router) {
+    // segment table of the routed rows (pass 1 + 2)
+    const int m = seg_max(T_, k, E);
+    TableWs tw = carve_table(base, m);
+    float* part = reinterpret_cast<float*>(base + table_bytes(m));
+    float* part_b = reinterpret_cast<float*>(base + table_bytes(m) + align_up((size_t)m * d * 4, 256));
+    hipLaunchKernelGGL(build_table_kernel, dim3(1), dim3(kTableThreads), 0, s, offsets, nullptr, E,
+                       kSegRows, 0, m, tw.n_entries, tw.table);
+    hipLaunchKernelGGL((route_bwd_dw_seg_kernel<T, 1>), dim3(m), dim3(256), 0, s, x, dl, row_src,
+                       tw.table, tw.n_entries, k, d, part, part_b);
+    const dim3 gred(E, (d + 255) / 256 < 8 ? (d + 255) / 256 : 8);
+    hipLaunchKernelGGL(route_bwd_dw_reduce_kernel, gred, dim3(256), 0, s, part, part_b, tw.table,
+                       tw.n_entries, E, d, dw_router, dbias);
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_route_bwd(const float* dgate, const int32_t* idx, const float* gate,
                             const float* logits, const uint8_t* alive, const void* x,
@@ -334,58 +547,15 @@ hipError_t launch_route_bwd(const float* dgate, const int32_t* idx, const float*
     if (dbias) hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, s, dbias, (size_t)E);
     return hipGetLastError();
   }
-  float* dl = static_cast<float*>(ws);
-  hipLaunchKernelGGL(route_bwd_dl_kernel, dim3((T_ + kDlThreads - 1) / kDlThreads),
-                     dim3(kDlThreads), 0, s, dgate, idx, gate, logits, alive, T_, E, k, renorm,
-                     dl, dlogits);
-  const int slots = renorm ? k : E;
-  const int32_t* ids = renorm ? idx : nullptr;
-  const dim3 gdx((unsigned)((T_ + 3) / 4)), gdw(E, (d / 8 + 31) / 32);
-  // renormalised gates: segment table of the routed rows (pass 1 + 2)
-  const int m = seg_max(T_, k, E);
-  char* base = static_cast<char*>(ws) + align_up((size_t)T_ * (k > E ? k : E) * sizeof(float), 256);
-  TableWs tw = carve_table(base, m);
-  float* part = reinterpret_cast<float*>(base + table_bytes(m));
-  float* part_b = reinterpret_cast<float*>(base + table_bytes(m) + align_up((size_t)m * d * 4, 256));
-  // dx (optional) and the weight gradients (optional, with dbias)
-  if (renorm && dw_router)
-    hipLaunchKernelGGL(build_table_kernel, dim3(1), dim3(kTableThreads), 0, s, offsets, nullptr, E,
-                       kSegRows, 0, m, tw.n_entries, tw.table);
-  const dim3 gred(E, (d + 255) / 256 < 8 ? (d + 255) / 256 : 8);
-  if (dtype == kDtypeBf16) {
-    if (dx)
-      hipLaunchKernelGGL(route_bwd_dx_kernel<bf16_t>, gdx, dim3(256), 0, s,
-                         static_cast<const bf16_t*>(w_router), ids, dl, T_, slots, d, accumulate_dx,
-                         static_cast<bf16_t*>(dx));
-    if (dw_router && renorm) {
-      hipLaunchKernelGGL((route_bwd_dw_seg_kernel<bf16_t, 1>), dim3(m), dim3(256), 0, s,
-                         static_cast<const bf16_t*>(x), dl, row_src, tw.table, tw.n_entries, k, d,
-                         part, part_b);
-      hipLaunchKernelGGL(route_bwd_dw_reduce_kernel, gred, dim3(256), 0, s, part, part_b,
-                         tw.table, tw.n_entries, E, d, dw_router, dbias);
-    } else if (dw_router) {
-      hipLaunchKernelGGL(route_bwd_dw_kernel<bf16_t>, gdw, dim3(256), 0, s,
-                         static_cast<const bf16_t*>(x), dl, T_, E, d,
-                         dw_router, dbias);
-    }
-  } else {
-    if (dx)
-      hipLaunchKernelGGL(route_bwd_dx_kernel<float>, gdx, dim3(256), 0, s,
-                         static_cast<const float*>(w_router), ids, dl, T_, slots, d, accumulate_dx,
-                         static_cast<float*>(dx));
-    if (dw_router && renorm) {
-      hipLaunchKernelGGL((route_bwd_dw_seg_kernel<float, 1>), dim3(m), dim3(256), 0, s,
-                         static_cast<const float*>(x), dl, row_src, tw.table, tw.n_entries, k, d,
-                         part, part_b);
-      hipLaunchKernelGGL(route_bwd_dw_reduce_kernel, gred, dim3(256), 0, s, part, part_b,
-                         tw.table, tw.n_entries, E, d, dw_router, dbias);
-    } else if (dw_router) {
-      hipLaunchKernelGGL(route_bwd_dw_kernel<float>, gdw, dim3(256), 0, s,
-                         static_cast<const float*>(x), dl, T_, E, d,
-                         dw_router, dbias);
-    }
-  }
-  return hipGetLastError();
+  if (dtype == kDtypeBf16)
+    return launch_route_bwd_t(dgate, idx, gate, logits, alive, static_cast<const bf16_t*>(x),
+                              static_cast<const bf16_t*>(w_router), offsets, row_src, T_, d, E, k,
+                              renorm, dlogits, dw_router, dbias, static_cast<bf16_t*>(dx),
+                              accumulate_dx, ws, s);
+  return launch_route_bwd_t(dgate, idx, gate, logits, alive, static_cast<const float*>(x),
+                            static_cast<const float*>(w_router), offsets, row_src, T_, d, E, k,
+                            renorm, dlogits, dw_router, dbias, static_cast<float*>(dx),
+                            accumulate_dx, ws, s);
 }
 
 }  // namespace laep
