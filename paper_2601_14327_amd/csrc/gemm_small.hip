@@ -282,51 +282,65 @@ hipError_t launch_small_pair(SmallParams g, SmallParams dn, int64_t R, bool gath
 
 }  // namespace
 
-// Row-tile height by estimated time: the k-steps a CU works through times the
-// measured time of one, per height (64 experts, d = 2048, f = 1024, 384 rows
-// each, where every kernel is bound by its own k-steps: 681 / 517 / 415 us at
-// 32 / 64 / 128 rows, 357 us for the 256-row kernels, whose tiles are 256
-// columns wide).  The experts' rows are taken as even; a few more or fewer
-// rows than a multiple of the height cost half a tile on average.  The
-// 256-row kernels hold one workgroup per CU, so few tiles leave whole rounds
-// partly idle; the others' workgroups share a CU, and one alone on its CU
-// takes 0.45 / 0.5 / 0.72 us a step (8 rows each, E = 16).  Below the estimate
-// lies the weights' stream from HBM, the same for every height.
-//   E, rows each: us at 32 / 64 / 128 / 256 rows (both products, d = 2048, f = 1024, E = 64;
-//   d = f = 1024, E = 16)
-//   64,  1: 105 / 112 / 138 / 163     16,   8:  21 /  23 /  29 / 42
-//   64, 32: 161 / 163 / 186 / 199     16,  64:  29 /  27 /  32 / 43
-//   64, 64: 205 / 184 / 193 / 206     16, 128:  42 /  37 /  34 / 48
-//   64, 96: 248 / 214 / 198 / 214     16, 512: 116 /  90 /  79 / 90
-//   64, 128: 297 / 250 / 255 / 221    16, 768: 173 / 131 / 111 / 100
+// Row-tile height by estimated time, root of the sum of squares of two parts:
+//  - the weights' stream from HBM, at the rate each kernel reaches with few
+//    rows (64 experts of 12.6 MB: 4.1 TB/s at 256 rows, 5.3-5.5 below);
+//  - the k-steps a CU works through, each at its measured time: 0.275 / 0.40 /
+//    0.64 us per tile at 32 / 64 / 128 rows (two or more workgroups sharing a
+//    CU; 0.45 / 0.5 / 0.72 for one alone), and 1.9 us per full 256-row tile
+//    (256 columns wide; a part of it for part of the rows, 0.8 more for each
+//    further, partly filled tile, 1.0 at least).  The 256-row kernels hold one
+//    workgroup per CU, so under two rounds of tiles whole rounds count.
+// The experts' rows are taken as even (the host does not know them); where
+// most loads no longer fit a whole number of tiles half a tile is added.
+// Measured, us for both products (estimates within 20 %, the choice within
+// 10 % of the best; d = 2048, f = 1024, E = 64, then d = f = 1024, E = 16):
+//   rows each   32 / 64 / 128 / 256-row tiles    rows each
+//     1         105 / 112 / 138 / 163              8          21 /  23 /  29 / 42
+//    32         161 / 163 / 186 / 199             64          29 /  27 /  32 / 43
+//    64         205 / 184 / 193 / 206            128          42 /  37 /  34 / 48
+//    96         248 / 214 / 198 / 214            512         116 /  90 /  79 / 90
+//   128         297 / 250 / 255 / 221            768         173 / 131 / 111 / 100
 int small_fwd_bm(int64_t R, int E, int d, int f) {
-  constexpr double kCUs = 256;
-  const double rows = (double)R / E;
-  const double live = R < E ? (double)R : (double)E;
-  auto product = [&](double bm, double cols_tiles, double nk, double step_us, double alone_us) {
-    // tiles of an expert: half a tile over, less where most loads fit the first
-    const double r = rows / bm;
-    const double over = r < 0.75 ? 0.0 : r < 1.0 ? 2.0 * (r - 0.75) : 0.5;
-    const double tiles = r + over < 1.0 ? 1.0 : r + over;
-    double rounds = live * tiles * cols_tiles / kCUs;
-    if (bm == 256 && rounds < 2) rounds = std::ceil(rounds);
-    return nk * (step_us * rounds > alone_us ? step_us * rounds : alone_us);
+  struct Kernel {
+    int bm;           // returned as 0 for the 256-row kernels
+    int cols_gu, cols_d;
+    double step_us, alone_us, stream_bytes_per_us;
   };
-  const double kg = d / 64.0, kd = f / 64.0;
+  const Kernel kernels[] = {
+      {256, ceil_div(f, 128), ceil_div(d, 256), 1.9, 1.0, 4.1e6},
+      {128, f / 64, ceil_div(d, 128), 0.64, 0.72, 5.3e6},
+      {64, f / 64, ceil_div(d, 128), 0.40, 0.5, 5.4e6},
+      {32, f / 64, ceil_div(d, 128), 0.275, 0.45, 5.5e6},
+  };
+  constexpr double kCUs = 256, kPartTile = 0.8;
+  const double rows = (double)R / E;
+  // experts that R rows spread at random reach
+  const double live = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)R));
   int best = 0;
-  double best_us = 0.9 * (product(256, ceil_div(f, 128), kg, 1.86, 1.86) +
-                          product(256, ceil_div(d, 256), kd, 1.86, 1.86));
-  const int bms[] = {128, 64, 32};
-  const double steps[] = {0.617, 0.414, 0.284}, alone[] = {0.72, 0.5, 0.45};
-  for (int i = 0; i < 3; ++i) {
-    const double us = product(bms[i], f / 64, kg, steps[i], alone[i]) +
-                      product(bms[i], ceil_div(d, 128), kd, steps[i], alone[i]);
-    if (us < best_us) {
+  double best_us = 0.0;
+  for (const Kernel& kn : kernels) {
+    const double r = rows / kn.bm;
+    const double over = r < 0.75 ? 0.0 : r < 1.0 ? 2.0 * (r - 0.75) : 0.5;
+    const double tiles = r + over > 1.0 ? r + over : 1.0;  // of one expert
+    auto product = [&](int cols, int K) {
+      const double per_cu = live * cols / kCUs;  // experts' column blocks
+      double us = kn.step_us * tiles * per_cu;
+      if (kn.bm == 256) {
+        us = (kn.step_us * r + kPartTile * (tiles - (r > 1.0 ? r : 1.0))) * per_cu;
+        const double rounds = tiles * per_cu;
+        if (rounds < 2.0) us *= std::ceil(rounds) / rounds;
+      }
+      return K / 64 * (us > kn.alone_us ? us : kn.alone_us);
+    };
+    const double us = std::hypot(live * 6.0 * d * f / kn.stream_bytes_per_us,
+                                 product(kn.cols_gu, d) + product(kn.cols_d, f));
+    if (best_us == 0.0 || us < best_us) {
       best_us = us;
-      best = bms[i];
+      best = kn.bm;
     }
   }
-  return best;
+  return best == 256 ? 0 : best;
 }
 
 hipError_t launch_ffn_fwd_small(int bm, const void* x, const void* w_gu, const void* w_d,
