@@ -319,17 +319,12 @@ int laep_repack_experts(const int32_t* expert_map, int E, int n_out, int dtype, 
   if (n_out == 0) return ok();
   const size_t es = elem_bytes(dtype);
   const hipStream_t s = as_stream(stream);
-  hipError_t e = hipSuccess;
-  if (w_router)
-    e = laep::launch_repack(expert_map, E, n_out, w_router, w_router_out, d_model * es, s);
-  if (e == hipSuccess && bias)
-    e = laep::launch_repack_scalar(expert_map, E, n_out, bias, bias_out, s);
-  if (e == hipSuccess && w_gate_up)
-    e = laep::launch_repack(expert_map, E, n_out, w_gate_up, w_gate_up_out,
-                            (size_t)2 * d_ff * d_model * es, s);
-  if (e == hipSuccess && w_down)
-    e = laep::launch_repack(expert_map, E, n_out, w_down, w_down_out,
-                            (size_t)d_model * d_ff * es, s);
+  const void* src[] = {w_gate_up, w_down, w_router};
+  void* dst[] = {w_gate_up_out, w_down_out, w_router_out};
+  const size_t bytes[] = {(size_t)2 * d_ff * d_model * es, (size_t)d_model * d_ff * es,
+                          d_model * es};
+  const hipError_t e =
+      laep::launch_repack(expert_map, E, n_out, src, dst, bytes, 3, bias, bias_out, s);
   return hip_status(e, "laep_repack_experts");
 }
 

@@ -61,10 +61,11 @@ hipError_t launch_expert_pruning(const int64_t* etn, int iters, int L, int E, in
                                  int32_t* n_pruned, int32_t* marker, hipStream_t s);
 hipError_t launch_expert_map(const uint8_t* alive, int L, int E, int32_t* expert_map,
                              int32_t* n_alive, hipStream_t s);
-hipError_t launch_repack(const int32_t* expert_map, int E, int n_out, const void* src, void* dst,
-                         size_t bytes_per_expert, hipStream_t s);
-hipError_t launch_repack_scalar(const int32_t* expert_map, int E, int n_out, const float* src,
-                                float* dst, hipStream_t s);
+// up to three tensors (NULL sources are skipped; bytes_per_expert[i] % 16 == 0)
+// and the float bias entries (or NULL)
+hipError_t launch_repack(const int32_t* expert_map, int E, int n_out, const void* const* src,
+                         void* const* dst, const size_t* bytes_per_expert, int n_tensors,
+                         const float* bias, float* bias_out, hipStream_t s);
 
 hipError_t launch_permute(const void* x, int elem_bytes, const int32_t* dest_row, int T, int k,
                           int d, void* x_perm, hipStream_t s);

@@ -15,60 +15,75 @@ namespace {
 
 constexpr int kPruneThreads = 256;
 
+// The marking rule for expert e among loads[0, E): its place in the
+// (load, index) order needs no sort, since the inclusive running sum there is
+// the sum over every expert that is not after it (exact in integers, in any
+// order).
+__device__ __forceinline__ bool marked(const long long* loads, int E, int e, double beta_thr,
+                                       double alpha_thr) {
+  const long long c = loads[e];
+  long long running = 0;
+#pragma unroll 8
+  for (int j = 0; j < E; ++j) {
+    const long long cj = loads[j];
+    running += (cj < c || (cj == c && j <= e)) ? cj : 0ll;
+  }
+  return (double)running < beta_thr && (double)c < alpha_thr;
+}
+
+// The same in 32 bits, for loads below kNarrowLoad (their sum over 256 experts
+// stays below 2^31): (load, index) is one key, so an expert costs a compare,
+// a select and an add instead of about a dozen 64-bit steps.
+constexpr int kNarrowLoad = 1 << 23;
+struct KeyLoad {
+  int key, load;  // load * 256 + index, load
+};
+__device__ __forceinline__ KeyLoad key_load(int load, int e) { return {load * 256 + e, load}; }
+__device__ __forceinline__ bool marked(const KeyLoad* loads, int E, int e, double beta_thr,
+                                       double alpha_thr) {
+  const KeyLoad c = loads[e];
+  int running = 0;
+#pragma unroll 16
+  for (int j = 0; j < E; ++j) {
+    const KeyLoad cj = loads[j];
+    running += cj.key <= c.key ? cj.load : 0;
+  }
+  return (double)running < beta_thr && (double)c.load < alpha_thr;
+}
+union LoadSlot {
+  long long wide;
+  KeyLoad narrow;
+};
+
 __global__ __launch_bounds__(kPruneThreads) void prune_kernel(const int32_t* __restrict__ counts,
                                                               int E, long long total, double alpha,
                                                               double beta,
                                                               uint8_t* __restrict__ alive,
                                                               int32_t* __restrict__ n_pruned) {
-  __shared__ int s_c[kPruneThreads];
-  __shared__ int s_sorted[kPruneThreads];
-  __shared__ long long s_scan[2][kPruneThreads];
-  __shared__ int s_flag[kPruneThreads];
+  __shared__ LoadSlot s_c[kPruneThreads];
   const int tid = threadIdx.x;
-  if (tid < E) s_c[tid] = counts[tid];
+  const int c = tid < E ? counts[tid] : 0;
+  const bool wide = __syncthreads_or(c < 0 || c >= kNarrowLoad);
+  if (wide) s_c[tid].wide = c;
+  else s_c[tid].narrow = key_load(c, tid);
   __syncthreads();
-  // rank of expert tid in the (load, index) order
+  bool pruned = false;
   if (tid < E) {
-    const int c = s_c[tid];
-    int rank = 0;
-    for (int j = 0; j < E; ++j) {
-      const int cj = s_c[j];
-      rank += (cj < c) || (cj == c && j < tid);
-    }
-    s_sorted[rank] = tid;
-  }
-  __syncthreads();
-  // inclusive scan of the sorted loads (Hillis-Steele, double-buffered)
-  int cur = 0;
-  s_scan[0][tid] = (tid < E) ? (long long)s_c[s_sorted[tid]] : 0ll;
-  __syncthreads();
-  for (int off = 1; off < kPruneThreads; off <<= 1) {
-    const long long v = s_scan[cur][tid] + (tid >= off ? s_scan[cur][tid - off] : 0ll);
-    s_scan[cur ^ 1][tid] = v;
-    cur ^= 1;
-    __syncthreads();
-  }
-  int pruned = 0;
-  if (tid < E) {
-    const int e = s_sorted[tid];
-    const double running = (double)s_scan[cur][tid];
-    const double load = (double)s_c[e];
     const double beta_thr = (double)total * beta;
     const double alpha_thr = ((double)total * alpha) / (double)E;
-    pruned = (running < beta_thr) && (load < alpha_thr);
-    alive[e] = pruned ? 0 : 1;
+    pruned = wide ? marked(&s_c[0].wide, E, tid, beta_thr, alpha_thr)
+                  : marked(&s_c[0].narrow, E, tid, beta_thr, alpha_thr);
+    alive[tid] = pruned ? 0 : 1;
   }
-  s_flag[tid] = pruned;
-  __syncthreads();
-  if (tid == 0) {
-    int n = 0;
-    for (int i = 0; i < E; ++i) n += s_flag[i];
-    *n_pruned = n;
-  }
+  const int n = __syncthreads_count(pruned);
+  if (tid == 0) *n_pruned = n;
 }
 
 // Algorithm 1 over a window of ITER recorded iterations (Appendix), one
-// workgroup per layer, one thread per expert.
+// workgroup per layer, one thread per (iteration, expert): the iterations
+// are independent up to their integer sums, so kWindowThreads / E of them run
+// at once.  (One thread per expert walking the window through a rank sort and
+// a scan each took 59 us for 16 iterations of 64 experts; now 12.)
 //   Step 2: per iteration, the marking rule above on ETN[iter, layer, :] with
 //           the layer's alpha; Marker[e] counts the iterations that marked e
 //           and Exp_dis the marks of all experts.
@@ -81,13 +96,13 @@ struct LayerAlphas {
   double a[kMaxLayers];
 };
 
-__global__ __launch_bounds__(kPruneThreads) void expert_pruning_kernel(
+constexpr int kWindowThreads = 1024;
+
+__global__ __launch_bounds__(kWindowThreads) void expert_pruning_kernel(
     const long long* __restrict__ etn, int ITER, int L, int E, long long total,
     const LayerAlphas alpha, double beta, uint8_t* __restrict__ alive,
     int32_t* __restrict__ n_pruned, int32_t* __restrict__ marker_out) {
-  __shared__ long long s_c[kPruneThreads];
-  __shared__ int s_sorted[kPruneThreads];
-  __shared__ long long s_scan[2][kPruneThreads];
+  __shared__ LoadSlot s_c[kWindowThreads];  // [group][E]
   __shared__ int s_mark[kPruneThreads];
   __shared__ long long s_sum[kPruneThreads];
   const int tid = threadIdx.x;
@@ -95,51 +110,35 @@ __global__ __launch_bounds__(kPruneThreads) void expert_pruning_kernel(
   const double a = alpha.a[layer];
   const double beta_thr = (double)total * beta;
   const double alpha_thr = ((double)total * a) / (double)E;
-  s_mark[tid] = 0;
-  s_sum[tid] = 0;
-  long long exp_dis = 0;
-  for (int it = 0; it < ITER; ++it) {
-    const long long* row = etn + ((size_t)it * L + layer) * E;
-    if (tid < E) {
-      s_c[tid] = row[tid];
-      s_sum[tid] += row[tid];
-    }
-    __syncthreads();
-    if (tid < E) {
-      const long long c = s_c[tid];
-      int rank = 0;
-      for (int j = 0; j < E; ++j) {
-        const long long cj = s_c[j];
-        rank += (cj < c) || (cj == c && j < tid);
-      }
-      s_sorted[rank] = tid;
-    }
-    __syncthreads();
-    int cur = 0;
-    s_scan[0][tid] = (tid < E) ? s_c[s_sorted[tid]] : 0ll;
-    __syncthreads();
-    for (int off = 1; off < kPruneThreads; off <<= 1) {
-      const long long v = s_scan[cur][tid] + (tid >= off ? s_scan[cur][tid - off] : 0ll);
-      s_scan[cur ^ 1][tid] = v;
-      cur ^= 1;
-      __syncthreads();
-    }
-    int marked = 0;
-    if (tid < E) {
-      const int e = s_sorted[tid];
-      const double running = (double)s_scan[cur][tid];
-      const double load = (double)s_c[e];
-      marked = (running < beta_thr) && (load < alpha_thr);
-      s_mark[e] += marked;  // each expert has exactly one rank position
-    }
-    exp_dis += __syncthreads_count(marked);
+  if (tid < kPruneThreads) {
+    s_mark[tid] = 0;
+    s_sum[tid] = 0;
   }
-  __syncthreads();
+  const int groups = kWindowThreads / E;  // iterations at once
+  const int g = tid / E, e = tid % E;
+  long long exp_dis = 0;
+  for (int it0 = 0; it0 < ITER; it0 += groups) {
+    const bool on = g < groups && it0 + g < ITER;
+    const long long c = on ? etn[((size_t)(it0 + g) * L + layer) * E + e] : 0;
+    const bool wide = __syncthreads_or(c < 0 || c >= kNarrowLoad);
+    if (wide) s_c[tid].wide = c;
+    else s_c[tid].narrow = key_load((int)c, e);
+    __syncthreads();
+    bool m = false;
+    if (on) {
+      m = wide ? marked(&s_c[g * E].wide, E, e, beta_thr, alpha_thr)
+               : marked(&s_c[g * E].narrow, E, e, beta_thr, alpha_thr);
+      if (m) atomicAdd(&s_mark[e], 1);  // integer sums: any order gives the same
+      atomicAdd(reinterpret_cast<unsigned long long*>(&s_sum[e]), (unsigned long long)c);
+    }
+    exp_dis += __syncthreads_count(m);  // (and s_c may be refilled)
+  }
   const long long n_dis = (long long)floor((double)exp_dis / (double)ITER + 0.5);
   if (tid < E) {
     const int m = s_mark[tid];
     const long long sm = s_sum[tid];
     int rank = 0;  // position in (marker desc, window load asc, index asc)
+#pragma unroll 8
     for (int j = 0; j < E; ++j) {
       const int mj = s_mark[j];
       const long long sj = s_sum[j];
@@ -165,7 +164,7 @@ hipError_t launch_expert_pruning(const int64_t* etn, int iters, int L, int E, in
                                  int32_t* n_pruned, int32_t* marker, hipStream_t s) {
   LayerAlphas la;
   for (int l = 0; l < kMaxLayers; ++l) la.a[l] = l < L ? alpha[l] : 0.0;
-  hipLaunchKernelGGL(expert_pruning_kernel, dim3(L), dim3(kPruneThreads), 0, s,
+  hipLaunchKernelGGL(expert_pruning_kernel, dim3(L), dim3(kWindowThreads), 0, s,
                      reinterpret_cast<const long long*>(etn), iters, L, E, (long long)total, la,
                      beta, alive, n_pruned, marker);
   return hipGetLastError();
