@@ -24,8 +24,19 @@
 // the 64-byte half lines of 32-wide k-steps.  One operand's k-step is a 32 KB
 // "half"; the LDS is a ring of five halves (A0 B0 A1 B1 A2 | B2 A3 ...), so
 // while step i computes, the B half of step i+1 and the A half of step i+2
-// are in flight: every half has at least one whole k-step (2048 MFMA cycles
-// per SIMD) to land.
+// are in flight: A has almost two k-steps (2048 MFMA cycles per SIMD each) to
+// land and B one.
+//
+// The order of issue inside a k-step is written out MFMA by MFMA: one fragment
+// read of the next k16 sub-step beside each MFMA, and the eight copies of a wave
+// one per two MFMAs in the two sub-steps after the step boundary.  Issued in one
+// burst after the boundary, the 64 copies of the eight waves queue behind each
+// other in the address unit (16 clocks each) ahead of the MFMAs that follow them.
+// Layer forward before / after: 8192 tokens top-8, d 2048, d_ff 1024, 888 / 868 us;
+// after pruning 853 / 821; 32768 rows, 16 experts, d 4096, d_ff 2048, 1528 / 1486.
+// One copy per four MFMAs over the whole k-step is slower (895 and 1545 us): B
+// then has less than a k-step to land.  Four waves of 128 x 128, a third fewer
+// fragment reads, run the k-loop no faster, and their epilogue spills.
 #include <type_traits>
 
 #include "common.hpp"
@@ -236,7 +247,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
   const int nt = te.nt;
 
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave / NWN, wn = wave % NWN;
 
   // per-thread byte offset of each LDS chunk it fills (k-step 0) within the
@@ -271,6 +282,12 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
     if (h & 1) dma_chunks<NH, NT>(dst, b_rsrc, b_voff, ks * 128, wave);
     else dma_chunks<NH, NT>(dst, a_rsrc, a_voff, ks * 128, wave);
   };
+  auto issue_chunk = [&](int h, int i) {  // chunk i of half h
+    const int ks = min(h >> 1, nk - 1);
+    char* dst = smem + (h % NSLOT) * HALF + i * NT * 16;
+    if (h & 1) dma_chunks<1, NT>(dst, b_rsrc, b_voff + i, ks * 128, wave);
+    else dma_chunks<1, NT>(dst, a_rsrc, a_voff + i, ks * 128, wave);
+  };
 
   // fragment LDS byte offsets within a half for k16 sub-step 0; sub-step s
   // reads logical chunk 2s + lane/32, i.e. byte offset ^ (32 s)
@@ -303,68 +320,68 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
     constexpr int NMM = TMV * TN;                // MFMAs per k16 sub-step
     u32x4_t fa0[TM], fb0[TN], fa1[TM], fb1[TN];
     // reads in the order the MFMAs consume them (B0 A0 B1 A1 ...)
-    auto read_frags = [&](const char* sa, const char* sb, int s, u32x4_t* fa, u32x4_t* fb) {
-      if (TMV == 0) return;
-#pragma unroll
-      for (int i = 0; i < (TMV > TN ? TMV : TN); ++i) {
-        if (i < TN) fb[i] = *reinterpret_cast<const u32x4_t*>(sb + (b_off[i] ^ (s << 5)));
-        if (i < TMV) fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_off[i] ^ (s << 5)));
-      }
+    auto read_frag = [&](const char* sa, const char* sb, int s, u32x4_t* fa, u32x4_t* fb, int n) {
+      const int pairs = TMV < TN ? TMV : TN;
+      const bool is_b = n < 2 * pairs ? (n & 1) == 0 : TN > TMV;
+      const int i = n < 2 * pairs ? n >> 1 : n - pairs;
+      if (is_b) fb[i] = *reinterpret_cast<const u32x4_t*>(sb + (b_off[i] ^ (s << 5)));
+      else fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_off[i] ^ (s << 5)));
     };
-    auto mma_step = [&](const u32x4_t* fa, const u32x4_t* fb) {
+    // One k16 sub-step: the MFMAs on (fa, fb), and beside them, in this order,
+    // the fragment reads (ga, gb) of the next sub-step and the NV copies of
+    // half h.
+    auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
+                        int s, u32x4_t* ga, u32x4_t* gb, auto nv_tag, int h) {
+      constexpr int NV = decltype(nv_tag)::value;
+      constexpr int MOST = NMM > NRD ? (NMM > 2 * NV ? NMM : 2 * NV) : (NRD > 2 * NV ? NRD : 2 * NV);
 #pragma unroll
-      for (int i = 0; i < TMV; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
+      for (int n = 0; n < MOST; ++n) {
+        if (n < NMM) {
+          const int i = n / TN, j = n % TN;
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               __builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j],
               0, 0, 0);
-    };
-    // the next sub-step's fragment reads alternate with this one's MFMAs
-    auto interleave = [&]() {
-      constexpr int NP = NRD < NMM ? NRD : NMM;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one DS read
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        if (n < NRD) {
+          read_frag(sa, sb, s, ga, gb, n);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        if (n < 2 * NV && (n & 1)) {
+          issue_chunk(h, n / 2);
+          __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+        }
       }
-      if (NMM > NP) __builtin_amdgcn_sched_group_barrier(0x008, NMM - NP, 0);
-      if (NRD > NP) __builtin_amdgcn_sched_group_barrier(0x100, NRD - NP, 0);
     };
+    using Copies = std::integral_constant<int, NH>;
+    using NoCopies = std::integral_constant<int, 0>;
 
-    // prologue: halves 0 .. 4 in flight, step 0 (halves 0, 1) landed
+    // prologue: halves 0 .. 3 in flight, step 0 (halves 0, 1) landed
 #pragma unroll
-    for (int h = 0; h < NSLOT; ++h) issue_half(h);
-    wait_vmcnt<3 * NH>();
+    for (int h = 0; h < NSLOT - 1; ++h) issue_half(h);
+    wait_vmcnt<2 * NH>();
     __builtin_amdgcn_s_barrier();
     int ia = 0, ib = 1;  // slots of the current step's A and B halves
-    read_frags(smem, smem + HALF, 0, fa0, fb0);
+#pragma unroll
+    for (int n = 0; n < NRD; ++n) read_frag(smem, smem + HALF, 0, fa0, fb0, n);
+    wait_lgkm0();  // nothing pending at the loop's entry: its waits then count its own reads
 
     for (int kt = 0; kt < nk; ++kt) {
       const char* sa = smem + ia * HALF;
       const char* sb = smem + ib * HALF;
-      read_frags(sa, sb, 1, fa1, fb1);
-      mma_step(fa0, fb0);
-      interleave();
-      read_frags(sa, sb, 2, fa0, fb0);
-      mma_step(fa1, fb1);
-      interleave();
-      read_frags(sa, sb, 3, fa1, fb1);
-      mma_step(fa0, fb0);
-      interleave();
+      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, Copies{}, 2 * kt + 4);
+      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, NoCopies{}, 0);
+      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, NoCopies{}, 0);
       // step boundary: this thread's reads of step kt are in registers and its
       // loads of step kt+1 have landed (only the A half of step kt+2 may still
       // be in flight); past the barrier the same holds for every thread, so the
-      // two halves of step kt are free: they receive B of kt+2 and A of kt+3.
+      // two halves of step kt are free: they receive B of kt+2 now and A of
+      // kt+3 in the next iteration.
       wait_vmcnt_lgkm0<NH>();
       __builtin_amdgcn_s_barrier();
-      issue_half(2 * kt + 5);
-      issue_half(2 * kt + 6);
       ia = ia + 2 >= NSLOT ? ia + 2 - NSLOT : ia + 2;
       ib = ib + 2 >= NSLOT ? ib + 2 - NSLOT : ib + 2;
-      read_frags(smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0);
-      mma_step(fa1, fb1);
-      interleave();
+      sub_step(fa1, fb1, smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0, Copies{}, 2 * kt + 5);
     }
   };
   // wave-uniform count of this wave's 32-row blocks that hold expert rows
@@ -388,9 +405,9 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
 // tile's k-loop ends, the first three halves of the next tile (k-step 0 and
 // the A half of k-step 1) go by LDS-DMA into ring slots 0-2 while the
 // epilogue stages the finished tile through slots 3-4 (64 KB, one wave row
-// of 128 rows per pass); slots 3-4 receive the next tile's halves 3 and 4
-// once the epilogue has read them back.  So the next tile's operand latency
-// runs under the epilogue instead of after it.
+// of 128 rows per pass); slot 3 receives the next tile's half 3 once the
+// epilogue has read it back.  So the next tile's operand latency runs under
+// the epilogue instead of after it.
 // ---------------------------------------------------------------------------
 // Epilogue staged through 64 KB at `stage` (forward only: no act_save).  The
 // down product's 256-column Y takes one wave row of 128 rows per pass as
@@ -641,6 +658,12 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
     if (h & 1) dma_chunks<NH, NT>(dst, b_rsrc, b_voff, ks * 128, wave_s);
     else dma_chunks<NH, NT>(dst, a_rsrc, a_voff, ks * 128, wave_s);
   };
+  auto issue_chunk = [&](int h, int i) {  // chunk i of half h
+    const int ks = min(h >> 1, nk - 1);
+    char* dst = smem + (h % NSLOT) * HALF + i * NT * 16;
+    if (h & 1) dma_chunks<1, NT>(dst, b_rsrc, b_voff + i, ks * 128, wave_s);
+    else dma_chunks<1, NT>(dst, a_rsrc, a_voff + i, ks * 128, wave_s);
+  };
 
   int a_off[TM], b_off[TN];
   const int lc0 = lane >> 5;
@@ -656,7 +679,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
   }
   f32x16_t acc[TM][TN];
 
-  // The k-loop of one tile, its halves 0 .. 4 already issued, for a wave
+  // The k-loop of one tile, its halves 0 .. 3 already issued, for a wave
   // whose first TMV 32-row blocks hold rows of the expert.  Thread 0 takes
   // the next tile from the counter at its start (the reply is read after the
   // loop; the loop's in-order waits only grow stricter for an older load).
@@ -666,33 +689,43 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
     constexpr int NRD = TMV > 0 ? TMV + TN : 0;
     constexpr int NMM = TMV * TN;
     u32x4_t fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    auto read_frags = [&](const char* sa, const char* sb, int s, u32x4_t* fa, u32x4_t* fb) {
-      if (TMV == 0) return;
-#pragma unroll
-      for (int i = 0; i < (TMV > TN ? TMV : TN); ++i) {
-        if (i < TN) fb[i] = *reinterpret_cast<const u32x4_t*>(sb + (b_off[i] ^ (s << 5)));
-        if (i < TMV) fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_off[i] ^ (s << 5)));
-      }
+    // reads in the order the MFMAs consume them (B0 A0 B1 A1 ...)
+    auto read_frag = [&](const char* sa, const char* sb, int s, u32x4_t* fa, u32x4_t* fb, int n) {
+      const int pairs = TMV < TN ? TMV : TN;
+      const bool is_b = n < 2 * pairs ? (n & 1) == 0 : TN > TMV;
+      const int i = n < 2 * pairs ? n >> 1 : n - pairs;
+      if (is_b) fb[i] = *reinterpret_cast<const u32x4_t*>(sb + (b_off[i] ^ (s << 5)));
+      else fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_off[i] ^ (s << 5)));
     };
-    auto mma_step = [&](const u32x4_t* fa, const u32x4_t* fb) {
+    // One k16 sub-step: the MFMAs on (fa, fb), and beside them, in this order,
+    // the fragment reads (ga, gb) of the next sub-step and the NV copies of
+    // half h.
+    auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
+                        int s, u32x4_t* ga, u32x4_t* gb, auto nv_tag, int h) {
+      constexpr int NV = decltype(nv_tag)::value;
+      constexpr int MOST = NMM > NRD ? (NMM > 2 * NV ? NMM : 2 * NV) : (NRD > 2 * NV ? NRD : 2 * NV);
 #pragma unroll
-      for (int i = 0; i < TMV; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
+      for (int n = 0; n < MOST; ++n) {
+        if (n < NMM) {
+          const int i = n / TN, j = n % TN;
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               __builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j],
               0, 0, 0);
-    };
-    auto interleave = [&]() {
-      constexpr int NP = NRD < NMM ? NRD : NMM;
-#pragma unroll
-      for (int i = 0; i < NP; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one DS read
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        if (n < NRD) {
+          read_frag(sa, sb, s, ga, gb, n);
+          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        if (n < 2 * NV && (n & 1)) {
+          issue_chunk(h, n / 2);
+          __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+        }
       }
-      if (NMM > NP) __builtin_amdgcn_sched_group_barrier(0x008, NMM - NP, 0);
-      if (NRD > NP) __builtin_amdgcn_sched_group_barrier(0x100, NRD - NP, 0);
     };
+    using Copies = std::integral_constant<int, NH>;
+    using NoCopies = std::integral_constant<int, 0>;
+
     // the fragment offsets are made opaque here, so the offsets each
     // instantiation derives from them are not hoisted out of the tile loop
     // (five instantiations' worth would stay live across every tile)
@@ -700,33 +733,25 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
     for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(a_off[i]));
 #pragma unroll
     for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(b_off[j]));
-    // halves 0 and 1 (step 0) landed: all but the last three halves issued
-    wait_vmcnt<3 * NH>();
+    // halves 0 and 1 (step 0) landed: all but the last two halves issued
+    wait_vmcnt<2 * NH>();
     __builtin_amdgcn_s_barrier();
     if (tid == 0) next_raw = atomicAdd(ctr, 1);
     int ia = 0, ib = 1;
-    read_frags(smem, smem + HALF, 0, fa0, fb0);
+#pragma unroll
+    for (int n = 0; n < NRD; ++n) read_frag(smem, smem + HALF, 0, fa0, fb0, n);
+    wait_lgkm0();  // nothing pending at the loop's entry: its waits then count its own reads
     for (int kt = 0; kt < nk; ++kt) {
       const char* sa = smem + ia * HALF;
       const char* sb = smem + ib * HALF;
-      read_frags(sa, sb, 1, fa1, fb1);
-      mma_step(fa0, fb0);
-      interleave();
-      read_frags(sa, sb, 2, fa0, fb0);
-      mma_step(fa1, fb1);
-      interleave();
-      read_frags(sa, sb, 3, fa1, fb1);
-      mma_step(fa0, fb0);
-      interleave();
+      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, Copies{}, 2 * kt + 4);
+      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, NoCopies{}, 0);
+      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, NoCopies{}, 0);
       wait_vmcnt_lgkm0<NH>();
       __builtin_amdgcn_s_barrier();
-      issue_half(2 * kt + 5);
-      issue_half(2 * kt + 6);
       ia = ia + 2 >= NSLOT ? ia + 2 - NSLOT : ia + 2;
       ib = ib + 2 >= NSLOT ? ib + 2 - NSLOT : ib + 2;
-      read_frags(smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0);
-      mma_step(fa1, fb1);
-      interleave();
+      sub_step(fa1, fb1, smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0, Copies{}, 2 * kt + 5);
     }
   };
 
@@ -743,7 +768,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
   finish_tile(raw);
 
 #pragma unroll
-  for (int h = 0; h < NSLOT; ++h) issue_half(h);
+  for (int h = 0; h < NSLOT - 1; ++h) issue_half(h);
   while (true) {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -777,7 +802,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
     });
     if (!more) break;
 #pragma unroll
-    for (int h = NPRE; h < NSLOT; ++h) issue_half(h);
+    for (int h = NPRE; h < NSLOT - 1; ++h) issue_half(h);
   }
 }
 
