@@ -198,7 +198,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
   const TileEntry te = p.table[entry];
 
   const int tid = threadIdx.x;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm = wave / NWN, wn = wave % NWN;
 
   // reduction extent of this tile (a multiple of 64 for the data gradients)
@@ -224,7 +224,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
       const int rr = r < te.rows ? r : te.rows - 1;  // rows past the expert: any valid row
       if (A_DY) {  // dY on load: the token row of routed row te.row0 + rr in dout
         const uint32_t s = (uint32_t)p.row_src[te.row0 + rr];
-        a_voff[i] = (s / (uint32_t)p.slots_k) * (uint32_t)p.lda * 2u + (uint32_t)(lc * 16);
+        a_voff[i] = div_slots(s, (uint32_t)p.slots_k, p.slots_magic) * (uint32_t)p.lda * 2u +
+                    (uint32_t)(lc * 16);
       } else {
         a_voff[i] = (uint32_t)(((long long)rr * p.lda + lc * 8) * 2);
       }
@@ -263,49 +264,43 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
     const int rem = kext - ks * 64;
     return rem > 0 ? (uint32_t)((long long)min(rem, 64) * ld * 2) : 0u;
   };
-  auto issue_half = [&](int h) {
+  auto issue_chunk = [&](int h, int i) {  // chunk i of this thread's NH of half h
     const int ks = min(h >> 1, nk - 1);
-    char* dst = smem + (h % kRingSlots) * kRingHalf;
-    if (h & 1) dma_half<NH, NT>(dst, b_tile + b_kstep * ks, extent(ks, p.ldb), b_voff, wave);
-    else dma_half<NH, NT>(dst, a_tile + a_kstep * ks, A_TR ? extent(ks, p.lda) : 0xffffffffu,
-                          a_voff, wave);
+    char* dst = smem + (h % kRingSlots) * kRingHalf + i * NT * 16;
+    if (h & 1)
+      dma_half<1, NT>(dst, b_tile + b_kstep * ks, extent(ks, p.ldb), b_voff + i, wave);
+    else
+      dma_half<1, NT>(dst, a_tile + a_kstep * ks, A_TR ? extent(ks, p.lda) : 0xffffffffu,
+                      a_voff + i, wave);
   };
-  // gathered B: the row_src entries of this thread's k-rows of step ks and a
-  // mask of the valid ones (rows past the expert, and the reloads past the
-  // last step, are not); then the DMA offsets they give (invalid rows fall
-  // outside x's buffer range).  Branch-free, and the loaded entries are only
-  // used at the next k-step, so no wait follows the loads: every load reads
-  // an entry of the expert's rows, and the validity is applied at use.
-  auto gather_idx = [&](int ks, uint32_t* raw, uint32_t& okm) {
-    okm = 0;
+  auto issue_half = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      const int kr = ks * 64 + b_kr[i];
-      const bool ok = ks < nk && kr < kext;
-      raw[i] = (uint32_t)p.row_src[te.row0 + (ok ? kr : 0)];
-      okm |= ok ? (1u << i) : 0u;
-    }
+    for (int i = 0; i < NH; ++i) issue_chunk(h, i);
   };
-  auto gather_voff = [&](const uint32_t* raw, uint32_t okm, uint32_t* v) {
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      const uint32_t off = (raw[i] / (uint32_t)p.slots_k) * (uint32_t)p.ldb * 2u + b_cb[i];
-      v[i] = (okm >> i) & 1u ? off : 0x80000000u;
-    }
+  // Gathered k-rows (B_GATHER; dW_d with dY on load): the row_src entry of
+  // k-row kr of step ks, any entry of the expert's rows past its end (the
+  // validity is applied at use), and the copy of one chunk through it: rows
+  // past the end get an offset beyond the operand's buffer range and read as
+  // zeros.  Branch-free.
+  auto row_id = [&](int ks, int kr) {
+    const int r = ks * 64 + kr;
+    return (uint32_t)p.row_src[te.row0 + (r < kext ? r : 0)];
   };
-  auto issue_b_gathered = [&](int h, const uint32_t* raw, uint32_t okm) {
-    uint32_t v[NH];
-    gather_voff(raw, okm, v);
-    dma_half<NH, NT>(smem + (h % kRingSlots) * kRingHalf, b_tile, p.b_extent, v, wave);
+  auto token_row = [&](uint32_t src) {  // src / slots_k
+    return div_slots(src, (uint32_t)p.slots_k, p.slots_magic);
+  };
+  auto issue_b_gathered = [&](int ks, int i, uint32_t src) {
+    const uint32_t v = ks * 64 + b_kr[i] < kext
+                           ? token_row(src) * (uint32_t)p.ldb * 2u + b_cb[i] : 0x80000000u;
+    dma_half<1, NT>(smem + ((2 * ks + 1) % kRingSlots) * kRingHalf + i * NT * 16, b_tile,
+                    p.b_extent, &v, wave);
   };
 
   // ---- dY formed on load (A_DY) ---------------------------------------------------
   // data gradient 1: the tile's rows are fixed, so each chunk's token-row
   // offset (a_voff, above) and its row's gate are loaded once; dW_d: the
   // k-rows change every step, so (as for a gathered B) each thread loads the
-  // row_src entries of its k-rows one step ahead of that step's A half, and the
-  // gates with the half
-  float ady_g[NH];
+  // row_src entries of its k-rows ahead of that step's A half
   int ady_kr[NH];
   uint32_t ady_cb[NH];
   if constexpr (A_DY && A_TR) {
@@ -319,37 +314,16 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
       ady_cb[i] = (uint32_t)(c * 2);
     }
   }
-  auto ady_idx = [&](int ks, uint32_t* raw, uint32_t& okm) {
-    okm = 0;
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      const int kr = ks * 64 + ady_kr[i];
-      const bool ok = ks < nk && kr < kext;
-      raw[i] = (uint32_t)p.row_src[te.row0 + (ok ? kr : 0)];
-      okm |= ok ? (1u << i) : 0u;
-    }
+  auto issue_a_gathered = [&](int ks, int i, uint32_t src) {
+    const uint32_t v = ks * 64 + ady_kr[i] < kext
+                           ? token_row(src) * (uint32_t)p.lda * 2u + ady_cb[i] : 0x80000000u;
+    dma_half<1, NT>(smem + ((2 * ks) % kRingSlots) * kRingHalf + i * NT * 16, a_tile, p.a_extent,
+                    &v, wave);
   };
-  // dW_d: the gathered A half of step ks (rows marked invalid fall outside
-  // dout's buffer range and read as zeros), and the gates of its k-rows
-  auto ady_issue_tr = [&](int ks, const uint32_t* raw, uint32_t okm, float* g) {
-    uint32_t v[NH];
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      const uint32_t off = (raw[i] / (uint32_t)p.slots_k) * (uint32_t)p.lda * 2u + ady_cb[i];
-      v[i] = (okm >> i) & 1u ? off : 0x80000000u;
-      g[i] = p.gate[raw[i]];
-    }
-    dma_half<NH, NT>(smem + ((2 * ks) % kRingSlots) * kRingHalf, a_tile, p.a_extent, v, wave);
-  };
-  // this thread's chunks of the A half of step ks, scaled in place (its own
-  // copies have landed; the next barrier publishes the result)
-  auto ady_scale = [&](int ks, const float* g) {
-    char* slot = smem + ((2 * ks) % kRingSlots) * kRingHalf;
-#pragma unroll
-    for (int i = 0; i < NH; ++i) {
-      u32x4_t* c = reinterpret_cast<u32x4_t*>(slot + (i * NT + tid) * 16);
-      *c = scale_bf16x8(*c, g[i]);
-    }
+  // this thread's chunk i of the A half of step ks
+  auto ady_chunk = [&](int ks, int i) {
+    return reinterpret_cast<u32x4_t*>(smem + ((2 * ks) % kRingSlots) * kRingHalf +
+                                      (i * NT + tid) * 16);
   };
 
   // ---- fragment offsets within a half, k16 sub-step 0 -------------------------------
@@ -391,136 +365,192 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
   // are not).  Weight-gradient tiles are always full.
   auto main_loop = [&](auto tmv_tag) {
     constexpr int TMV = decltype(tmv_tag)::value;
+    constexpr int NRD = TMV > 0 ? TMV + TN : 0;  // fragments per k16 sub-step
+    constexpr int NMM = TMV * TN;                // MFMAs per k16 sub-step
+    constexpr int A_RD = A_TR ? 2 : 1;           // DS reads per A fragment
     u32x4_t fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    // k16 sub-step s of a k-step: K-contiguous fragments flip the logical
-    // chunk by 2 (byte offset ^ 32 s); TR fragments move down 16 k-rows
-    auto read_frags = [&](const char* sa, const char* sb, int s, u32x4_t* fa, u32x4_t* fb) {
-      if (TMV == 0) return;
-#pragma unroll
-      for (int i = 0; i < (TMV > TN ? TMV : TN); ++i) {
-        if (i < TN) fb[i] = read_tr_frag(sb, b_o1[i] + s * 16 * kTrRowB, b_o2[i] + s * 16 * kTrRowB);
-        if (i < TMV) {
-          if (A_TR) fa[i] = read_tr_frag(sa, a_o1[i] + s * 16 * kTrRowB, a_o2[i] + s * 16 * kTrRowB);
-          else fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_o1[i] ^ (s << 5)));
-        }
+    // fragment n of k16 sub-step s of a k-step, in the order the MFMAs consume
+    // them (B0 A0 B1 A1 A2 ...).  K-contiguous fragments flip the logical chunk
+    // by 2 (byte offset ^ 32 s); TR fragments move down 16 k-rows
+    auto read_frag = [&](const char* sa, const char* sb, int s, u32x4_t* fa, u32x4_t* fb, int n) {
+      const int pairs = TMV < TN ? TMV : TN;
+      const bool is_b = n < 2 * pairs ? (n & 1) == 0 : TN > TMV;
+      const int i = n < 2 * pairs ? n >> 1 : n - pairs;
+      const int down = s * 16 * kTrRowB;
+      if (is_b) {
+        fb[i] = read_tr_frag(sb, b_o1[i] + down, b_o2[i] + down);
+        __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      } else {
+        if (A_TR) fa[i] = read_tr_frag(sa, a_o1[i] + down, a_o2[i] + down);
+        else fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_o1[i] ^ (s << 5)));
+        __builtin_amdgcn_sched_group_barrier(0x100, A_RD, 0);
       }
     };
-    auto mma_step = [&](const u32x4_t* fa, const u32x4_t* fb) {
+    // One k16 sub-step: the MFMAs on (fa, fb) and beside each of them, in this
+    // order, one fragment (ga, gb) of the next sub-step and what beside(n)
+    // issues.  The MFMA pipe is kept busy by the order alone: reads issued as a
+    // block are waited for as a block, and a block of copies queues in the
+    // address unit (16 clocks each for every wave) ahead of the MFMAs that
+    // follow it.
+    auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
+                        int s, u32x4_t* ga, u32x4_t* gb, auto&& beside) {
 #pragma unroll
-      for (int i = 0; i < TMV; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
+      for (int n = 0; n < 8; ++n) {
+        if (n < NMM) {
+          const int i = n / TN, j = n % TN;
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
               __builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j],
               0, 0, 0);
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        }
+        if (n < NRD) read_frag(sa, sb, s, ga, gb, n);
+        beside(n);
+      }
     };
+    static_assert(NMM <= 8 && NRD <= 8 && NH == 4, "a sub-step's eight slots");
+    auto one_vmem = [] { __builtin_amdgcn_sched_group_barrier(0x010, 1, 0); };
 
-    // prologue: halves 0 .. 4 in flight, step 0 (halves 0, 1) landed
-    uint32_t idx_next[NH], ok_next = 0;  // gathered B: row_src of the next B half to issue
-    // dY on load: the gates of the A halves landed or in flight (dW_d: of
-    // steps kt+1 and kt+2 at step kt's boundary) and the row_src entries of the
-    // next A half to issue
-    float ady_g1[NH], ady_g2[NH];
-    uint32_t ady_src[NH], ady_ok = 0;
+    // prologue: the halves of steps 0 and 1 in flight, step 0 landed
+    uint32_t src[NH], src_next[NH];  // gathered k-rows: row ids of the next half to issue
+    float g[NH];                     // dY on load: gates of the next A half to scale
     if constexpr (A_DY) {
       float g0[NH];
       if constexpr (A_TR) {
-        uint32_t s0[NH], s1[NH], s2[NH], ok0, ok1, ok2;
-        ady_idx(0, s0, ok0);
-        ady_idx(1, s1, ok1);
-        ady_idx(2, s2, ok2);
-        ady_idx(3, ady_src, ady_ok);
-        ady_issue_tr(0, s0, ok0, g0);
+        uint32_t s0[NH], s1[NH];
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          s0[i] = row_id(0, ady_kr[i]);
+          s1[i] = row_id(1, ady_kr[i]);
+          src[i] = row_id(2, ady_kr[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          g0[i] = p.gate[s0[i]];
+          issue_a_gathered(0, i, s0[i]);
+        }
         issue_half(1);
-        ady_issue_tr(1, s1, ok1, ady_g1);
+#pragma unroll
+        for (int i = 0; i < NH; ++i) issue_a_gathered(1, i, s1[i]);
         issue_half(3);
-        ady_issue_tr(2, s2, ok2, ady_g2);
+#pragma unroll
+        for (int i = 0; i < NH; ++i) g[i] = p.gate[s1[i]];
+        wait_vmcnt<3 * NH>();
       } else {
 #pragma unroll
         for (int i = 0; i < NH; ++i) {   // data gradient 1: the chunk rows' gates, once
           const int rr = min((i * NT + tid) >> 3, te.rows - 1);
-          ady_g[i] = p.gate[p.row_src[te.row0 + rr]];
-          g0[i] = ady_g[i];
+          g0[i] = g[i] = p.gate[p.row_src[te.row0 + rr]];
         }
 #pragma unroll
-        for (int h = 0; h < kRingSlots; ++h) issue_half(h);
+        for (int h = 0; h < kRingSlots - 1; ++h) issue_half(h);
+        wait_vmcnt<2 * NH>();
       }
-      wait_vmcnt<3 * NH>();
-      ady_scale(0, g0);
-      wait_lgkm0();
-    } else if constexpr (B_GATHER) {
-      uint32_t idx0[NH], idx1[NH], ok0, ok1;
-      gather_idx(0, idx0, ok0);
-      gather_idx(1, idx1, ok1);
-      gather_idx(2, idx_next, ok_next);
-      issue_half(0);
-      issue_b_gathered(1, idx0, ok0);
-      issue_half(2);
-      issue_b_gathered(3, idx1, ok1);
-      issue_half(4);
-    } else {
 #pragma unroll
-      for (int h = 0; h < kRingSlots; ++h) issue_half(h);
+      for (int i = 0; i < NH; ++i) {
+        u32x4_t* c = ady_chunk(0, i);
+        *c = scale_bf16x8(*c, g0[i]);
+      }
+      wait_lgkm0();
+    } else {
+      if constexpr (B_GATHER) {
+        uint32_t s0[NH], s1[NH];
+#pragma unroll
+        for (int i = 0; i < NH; ++i) {
+          s0[i] = row_id(0, b_kr[i]);
+          s1[i] = row_id(1, b_kr[i]);
+          src[i] = row_id(2, b_kr[i]);
+        }
+        issue_half(0);
+#pragma unroll
+        for (int i = 0; i < NH; ++i) issue_b_gathered(0, i, s0[i]);
+        issue_half(2);
+#pragma unroll
+        for (int i = 0; i < NH; ++i) issue_b_gathered(1, i, s1[i]);
+      } else {
+#pragma unroll
+        for (int h = 0; h < kRingSlots - 1; ++h) issue_half(h);
+      }
+      wait_vmcnt<2 * NH>();
     }
-    if constexpr (!A_DY) wait_vmcnt<3 * NH>();
     __builtin_amdgcn_s_barrier();
     int ia = 0, ib = 1;  // slots of the current step's A and B halves
-    read_frags(smem, smem + kRingHalf, 0, fa0, fb0);
+#pragma unroll
+    for (int n = 0; n < NRD; ++n) read_frag(smem, smem + kRingHalf, 0, fa0, fb0, n);
+    wait_lgkm0();
     for (int kt = 0; kt < nk; ++kt) {
       const char* sa = smem + ia * kRingHalf;
       const char* sb = smem + ib * kRingHalf;
-      read_frags(sa, sb, 1, fa1, fb1);
-      mma_step(fa0, fb0);
-      read_frags(sa, sb, 2, fa0, fb0);
-      mma_step(fa1, fb1);
-      if constexpr (A_DY) {
-        // dY on load: this thread's copies of the A half of step kt+1 have
-        // landed once only the halves issued after it may be in flight (two
-        // iterations' worth: 2 or, for dW_d with its row_src and gate loads, 4
-        // groups of NH); scale them here, beside the MFMAs, so the LDS round
-        // trip stays off the step boundary (the boundary's lgkmcnt(0) and
-        // barrier publish them)
-        wait_vmcnt<(A_TR ? 8 : 4) * NH>();
-        ady_scale(kt + 1, A_TR ? ady_g1 : ady_g);
-      }
-      read_frags(sa, sb, 3, fa1, fb1);
-      mma_step(fa0, fb0);
+      // A of step kt+2, one copy per two MFMAs (dW_d with dY on load: and the
+      // row ids of step kt+3)
+      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, [&](int n) {
+        if constexpr (A_DY && A_TR) {
+          if (n & 1) {
+            issue_a_gathered(kt + 2, n / 2, src[n / 2]);
+          } else {
+            src_next[n / 2] = row_id(kt + 3, ady_kr[n / 2]);
+          }
+          one_vmem();
+        } else {
+          if (n & 1) {
+            issue_chunk(2 * kt + 4, n / 2);
+            one_vmem();
+          }
+        }
+      });
+      // dY on load: this thread's copies of the A half of step kt+1 have landed
+      // once only what was issued after them may be in flight: B of kt+1 and A of
+      // kt+2, and for dW_d the gates of kt+1 and the row ids of kt+3.  It scales
+      // its chunks in place, read beside sub-step 1, scaled and written beside
+      // sub-step 2; the boundary's lgkmcnt(0) and barrier publish them.
+      u32x4_t dy[NH];
+      if constexpr (A_DY) wait_vmcnt<(A_TR ? 4 : 2) * NH>();
+      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, [&](int n) {
+        if constexpr (A_DY) {
+          if (n < NH) {
+            dy[n] = *ady_chunk(kt + 1, n);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+          }
+        }
+      });
+      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, [&](int n) {
+        if constexpr (A_DY) {
+          if (n & 1) {
+            *ady_chunk(kt + 1, n / 2) = scale_bf16x8(dy[n / 2], g[n / 2]);
+            __builtin_amdgcn_sched_group_barrier(0x002, 20, 0);
+            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+          }
+        }
+      });
       // step boundary: this thread's reads of step kt are in registers and its
-      // loads of step kt+1 have landed (only the A half of step kt+2 may still
-      // be in flight); past the barrier the same holds for every thread, so the
-      // two halves of step kt are free: they receive B of kt+2 and A of kt+3.
-      wait_vmcnt_lgkm0<NH>();
+      // loads of step kt+1 have landed (only the A half of step kt+2, and for
+      // dW_d with dY on load the row ids beside it, may still be in flight); past
+      // the barrier the same holds for every thread, so the slots of step kt are
+      // free: its B slot receives A of kt+3 in the next iteration, its A slot B of
+      // kt+2 now (gathered: through the row ids loaded one step ago, then those
+      // of kt+3; dW_d with dY on load: with the gates of kt+2)
+      wait_vmcnt_lgkm0<(A_DY && A_TR ? 2 : 1) * NH>();
       __builtin_amdgcn_s_barrier();
-      if constexpr (A_DY && A_TR) {
-        // dW_d: the gates move down a step; the A half of kt+3 (row_src loaded
-        // last iteration) with its gates; the row_src entries of kt+4 first,
-        // so the next boundary's wait covers them
-#pragma unroll
-        for (int i = 0; i < NH; ++i) ady_g1[i] = ady_g2[i];
-        uint32_t src3[NH];
-#pragma unroll
-        for (int i = 0; i < NH; ++i) src3[i] = ady_src[i];
-        const uint32_t ok3 = ady_ok;
-        ady_idx(kt + 4, ady_src, ady_ok);
-        issue_half(2 * kt + 5);
-        ady_issue_tr(kt + 3, src3, ok3, ady_g2);
-      } else if constexpr (B_GATHER) {
-        // the offsets of B(kt + 2) from the entries loaded last iteration; the
-        // entries of step kt + 3 are loaded before this iteration's halves,
-        // so the next boundary's wait covers them
-        uint32_t v[NH];
-        gather_voff(idx_next, ok_next, v);
-        gather_idx(kt + 3, idx_next, ok_next);
-        dma_half<NH, NT>(smem + ((2 * kt + 5) % kRingSlots) * kRingHalf, b_tile, p.b_extent, v,
-                         wave);
-      } else {
-        issue_half(2 * kt + 5);
-      }
-      if constexpr (!(A_DY && A_TR)) issue_half(2 * kt + 6);
       ia = ia + 2 >= kRingSlots ? ia + 2 - kRingSlots : ia + 2;
       ib = ib + 2 >= kRingSlots ? ib + 2 - kRingSlots : ib + 2;
-      read_frags(smem + ia * kRingHalf, smem + ib * kRingHalf, 0, fa0, fb0);
-      mma_step(fa1, fb1);
+      sub_step(fa1, fb1, smem + ia * kRingHalf, smem + ib * kRingHalf, 0, fa0, fb0, [&](int n) {
+        if constexpr (B_GATHER) {
+          if (n & 1) issue_b_gathered(kt + 2, n / 2, src[n / 2]);
+          else src_next[n / 2] = row_id(kt + 3, b_kr[n / 2]);
+          one_vmem();
+        } else {
+          if (n & 1) {
+            issue_chunk(2 * kt + 5, n / 2);
+            one_vmem();
+          } else if constexpr (A_DY && A_TR) {
+            g[n / 2] = p.gate[src[n / 2]];
+            one_vmem();
+          }
+        }
+      });
+      if constexpr (B_GATHER || (A_DY && A_TR)) {
+#pragma unroll
+        for (int i = 0; i < NH; ++i) src[i] = src_next[i];
+      }
     }
     // no LDS-DMA may still be writing when the LDS is reused for staging
     wait_vmcnt<0>();
@@ -745,6 +775,7 @@ hipError_t launch_ffn_bwd_bf16(const void* dy, const void* x_perm, const void* a
   wd.lda = d;
   wd.row_src = row_src;
   wd.slots_k = slots_k;
+  wd.slots_magic = slots_magic(slots_k);
   wd.gate = gate;
   wd.a_extent = (uint32_t)(x_rows * d * 2);
   wd.B = h_fwd ? static_cast<const bf16_t*>(h_fwd) : Hb;
@@ -763,7 +794,6 @@ hipError_t launch_ffn_bwd_bf16(const void* dy, const void* x_perm, const void* a
   wg.B = static_cast<const bf16_t*>(x_perm);   // token rows x when gathering
   wg.ldb = d;
   wg.row_src = row_src;
-  wg.slots_k = slots_k;
   wg.b_extent = (uint32_t)(x_rows * d * 2);
   wg.Mw = 2 * f;
   wg.N = d;
@@ -800,6 +830,7 @@ hipError_t launch_ffn_bwd_bf16(const void* dy, const void* x_perm, const void* a
   g.lda = d;
   g.row_src = row_src;
   g.slots_k = slots_k;
+  g.slots_magic = slots_magic(slots_k);
   g.gate = gate;
   g.a_extent = (uint32_t)(x_rows * d * 2);
   g.B = static_cast<const bf16_t*>(w_d);

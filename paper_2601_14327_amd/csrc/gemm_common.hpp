@@ -33,6 +33,7 @@ struct GemmParams {
   int accumulate;
   const int32_t* row_src;  // gathered A rows: row r of the product is A row row_src[r] / slots_k
   int slots_k;
+  uint32_t slots_magic;    // of slots_k, see div_slots()
   // gate-scaled scatter of the down product (one slot per token): routed row r
   // also goes to out_tok row row_src[r] / slots_k, times gate[row_src[r]]
   const float* gate;
@@ -118,6 +119,15 @@ __device__ __forceinline__ void dma_chunks(char* dst, __amdgpu_buffer_rsrc_t rsr
   for (int i = 0; i < NC; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)(dst + (i * NT + wave * 64) * 16),
                                              16, voff[i], soff, 0, POLICY);
+}
+
+// n / k for 0 <= n < 2^31 in five integer instructions, with the magic
+// floor((2^32 - 1) / k): n * magic / 2^32 lies in (n/k - 1/2, n/k], so its whole
+// part is the quotient or one below it.
+inline uint32_t slots_magic(int k) { return k > 0 ? 0xffffffffu / (uint32_t)k : 0u; }
+__device__ __forceinline__ uint32_t div_slots(uint32_t n, uint32_t k, uint32_t magic) {
+  const uint32_t q = __umulhi(n, magic);
+  return q + (n - q * k >= k ? 1u : 0u);
 }
 
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }
