@@ -11,8 +11,8 @@ together more than twice the 256 MB MALL) so the activations are not
 cache-resident.  With one slot per token (shard,
 shard_bwd) the combine folds into the FFN call as well (the down projection
 writes each row, times its gate, to its token row).  Training steps write no
-x_perm and no dy_perm: the weight gradient gathers the token rows through
-row_src as well, and the expert backward forms dY = g * dout on load.
+x_perm: the weight gradient gathers the token rows through row_src as well;
+dY = g * dout is written once by the combine backward.
 
 Prints ONE JSON line:
   value        tokens/s of the whole step (wall clock over the timed steps,
@@ -291,13 +291,11 @@ class Setup:
                 p.dw_gate_up = torch.empty(self.wgu.shape, dtype=torch.float32, device=self.dev)
                 p.dw_down = torch.empty(self.wd.shape, dtype=torch.float32, device=self.dev)
             out += [("combine_bwd", lambda: L.moe_combine_bwd(
-                self.dout, p.y_perm, gate, p.dest_row, dy_perm=p.dy_perm, dgate=p.dgate,
-                want_dy=p.dy_perm is not None))]
+                self.dout, p.y_perm, gate, p.dest_row, dy_perm=p._dy, dgate=p.dgate))]
             if w.routed:   # the router's weight gradients on a side stream, beside the FFN's
                 out += [("route_bwd_w", lambda: p.route_backward_weights_async(x, self.wr))]
             out += [("ffn_bwd", lambda: L.moe_grouped_ffn_bwd_gather(
-                        None, x, p.row_src, w.k, p.act_save, self.wgu, self.wd,
-                        p.offsets, dout=self.dout, topk_gate=gate,
+                        p._dy, x, p.row_src, w.k, p.act_save, self.wgu, self.wd, p.offsets,
                         h_fwd=L.ffn_fwd_h_view(p.ws_ffn, R, w.d_ff, p.dtype),
                         dw_gate_up=p.dw_gate_up, dw_down=p.dw_down, ws=p.ws_bwd,
                         dx_perm=p.dx_perm) if p.fused else L.moe_grouped_ffn_bwd(
@@ -322,11 +320,8 @@ class Setup:
             "counts": T * k * 4 + 2 * (E + 1) * 4 + R * 4,
             "permute": T * d * e + R * d * e + R * 4,
             "combine": R * d * e + T * d * e + 2 * R * 4,
-            # dout and y_perm read, gates and dest rows read, dgate written; dy_perm
-            # written only when the plan keeps it (the fused backward forms dY
-            # on load instead)
-            "combine_bwd": T * d * e + R * d * e + 3 * R * 4
-            + (R * d * e if getattr(self.plan, "dy_perm", None) is not None else 0),
+            # dout and y_perm read, gates and dest rows read, dY and dgate written
+            "combine_bwd": T * d * e + 2 * R * d * e + 3 * R * 4,
             "permute_bwd": R * d * e + T * d * e + R * 4,
             # dx read + written, W_r once, x once (summed into dW_r), dgate/gates/ids, dW_r
             "route_bwd": 2 * T * d * e + E * d * e + T * d * e + 3 * T * k * 4 + E * d * 4,
