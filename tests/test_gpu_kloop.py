@@ -22,16 +22,18 @@ def test_backward_kloop_edges(d, f, k):
     counts = [0, 1, 31, 33, 63, 65, 127, 129, 193, 225, 257, 420]
     E = len(counts)
     rng = np.random.default_rng(d + f + k)
-    # any slots: the FFN calls take each routed row's token as row_src / k
-    ids = rng.permutation(np.repeat(np.arange(E), counts))
-    ids = ids[:len(ids) // k * k].reshape(-1, k).astype(np.int32)
-    T, R = ids.shape[0], ids.size
+    # slots counted one by one (a token may hold an expert twice): the FFN calls
+    # take the token of routed row r as row_src[r] / k
+    ids = rng.permutation(np.repeat(np.arange(E), counts)).astype(np.int32)
+    R = len(ids) // k * k
+    T = R // k
     c = random_case(d + k, T=T, d_model=d, E=E, k=1, d_ff=f, dtype="bf16")
     x, wgu, wd = dev(c["x"], BF), dev(c["w_gate_up"], BF), dev(c["w_down"], BF)
     gate_h = rng.uniform(0.05, 1.0, (T, k)).astype(np.float32)
     dout_h = rng.standard_normal((T, d)).astype(np.float32)
     gate, dout = dev(gate_h, torch.float32), dev(dout_h, BF)
-    _, offsets, dest, src = laep.moe_expert_counts(dev(ids, torch.int32), E, want_row_src=True)
+    _, offsets, dest, src = laep.moe_expert_counts(dev(ids[:R].reshape(R, 1), torch.int32), E,
+                                                      want_row_src=True)
     case(f"k-loop edges T={T} k={k} d={d} f={f}")
     xp = laep.moe_permute(x, dest, k)
     ws = torch.empty(laep.workspace_bytes(laep.LAEP_CALL_FFN_FWD, R, 1, E, d, f),
