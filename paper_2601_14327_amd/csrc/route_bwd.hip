@@ -6,8 +6,10 @@
 // Renormalised gates make dl zero outside the k selected experts, so dx is a
 // k-term weighted sum of W_r rows (like the combine) and dW_r[e] a weighted
 // sum over the expert's routed rows, which moe_expert_counts already lists
-// in expert order (row_src).  Full-softmax gates make dl dense over the alive
-// experts; dx then sums over all E experts and dW_r over all T tokens.
+// in expert order (row_src); with few experts, or many slots, the dense product
+// over all tokens is faster than gathering them.  Full-softmax gates make dl
+// dense over the alive experts; dx then sums over all E experts and dW_r over all
+// T tokens.
 // Every sum runs in a fixed order: results are deterministic.
 #include "common.hpp"
 #include "internal.hpp"
@@ -18,26 +20,56 @@ namespace {
 
 constexpr int kDlThreads = 256;
 
-// Renormalised gates, one thread per token: dl_slot[t, j] =
-// g_j (dg_j - sum_i g_i dg_i) (0 for unrouted slots).  dlogits (optional)
-// gets the dense [T, E] gradient.
+// Renormalised gates: dl_slot[t, j] = g_j (dg_j - sum_i g_i dg_i) (0 for
+// unrouted slots).  dl_dense and dlogits (both optional) get the dense [T, E]
+// gradient.  One wave per token: lane j holds slot j (then j + 64, ...), lane e
+// writes experts e, e + 64, ..., so the slots are loaded and the rows written in
+// whole lines and the sum is still taken in slot order.
 __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_kernel(
     const float* __restrict__ dgate, const int32_t* __restrict__ idx,
     const float* __restrict__ gate, int T, int E, int k, float* __restrict__ dl_out,
-    float* __restrict__ dlogits) {
-  const int t = blockIdx.x * kDlThreads + threadIdx.x;
+    float* __restrict__ dl_dense, float* __restrict__ dlogits) {
+  const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * (kDlThreads / 64) +
+                                               (int)(threadIdx.x >> 6));
   if (t >= T) return;
+  const int lane = threadIdx.x & 63;
   const size_t s0 = (size_t)t * k;
+  auto from_lane = [](float v, int l) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+  };
   float s = 0.0f;
-  for (int j = 0; j < k; ++j)
-    if (idx[s0 + j] >= 0) s += gate[s0 + j] * dgate[s0 + j];
-  if (dlogits)
-    for (int e = 0; e < E; ++e) dlogits[(size_t)t * E + e] = 0.0f;
-  for (int j = 0; j < k; ++j) {
-    const int e = idx[s0 + j];
-    const float v = e >= 0 ? gate[s0 + j] * (dgate[s0 + j] - s) : 0.0f;
-    dl_out[s0 + j] = v;
-    if (dlogits && e >= 0) dlogits[(size_t)t * E + e] = v;
+  for (int j0 = 0; j0 < k; j0 += 64) {
+    const int n = min(64, k - j0);
+    float p = 0.0f;
+    if (lane < n && idx[s0 + j0 + lane] >= 0)
+      p = gate[s0 + j0 + lane] * dgate[s0 + j0 + lane];
+    for (int j = 0; j < n; ++j) s += from_lane(p, j);
+  }
+  constexpr int EPL = 4;  // at most 256 experts
+  float row[EPL] = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int j0 = 0; j0 < k; j0 += 64) {
+    const int n = min(64, k - j0);
+    int e = -1;
+    float v = 0.0f;
+    if (lane < n) {
+      e = idx[s0 + j0 + lane];
+      v = e >= 0 ? gate[s0 + j0 + lane] * (dgate[s0 + j0 + lane] - s) : 0.0f;
+      dl_out[s0 + j0 + lane] = v;
+    }
+    if (dl_dense || dlogits)
+      for (int j = 0; j < n; ++j) {
+        const int ej = __builtin_amdgcn_readlane(e, j);
+        const float vj = from_lane(v, j);
+#pragma unroll
+        for (int u = 0; u < EPL; ++u) row[u] = ej == lane + 64 * u ? vj : row[u];
+      }
+  }
+#pragma unroll
+  for (int u = 0; u < EPL; ++u) {
+    const int e = lane + 64 * u;
+    if (e >= E) continue;
+    if (dl_dense) dl_dense[(size_t)t * E + e] = row[u];
+    if (dlogits) dlogits[(size_t)t * E + e] = row[u];
   }
 }
 
@@ -180,10 +212,24 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
 enum { kDx = 0, kDw = 1 };
 constexpr int kDenseBM = 64, kDenseBN = 128, kDenseKC = 32;
 
+__device__ __forceinline__ float widen(float v) { return v; }
+__device__ __forceinline__ float widen(bf16_t v) { return lo_bf16(v); }
+
 template <typename T> struct Wide8;  // 8 consecutive elements -> fp32
 template <> struct Wide8<bf16_t> {
   u32x4_t r;
   __device__ __forceinline__ void zero() { r = u32x4_t{0u, 0u, 0u, 0u}; }
+  // infinities and NaNs to zero; true if there were any
+  __device__ __forceinline__ bool drop_nonfinite() {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool lo = (r[i] & 0x7f80u) == 0x7f80u, hi = (r[i] & 0x7f800000u) == 0x7f800000u;
+      bad |= lo | hi;
+      r[i] &= (lo ? 0xffff0000u : ~0u) & (hi ? 0xffffu : ~0u);
+    }
+    return bad;
+  }
   __device__ __forceinline__ void load(const bf16_t* p) {
     r = *reinterpret_cast<const u32x4_t*>(p);
   }
@@ -195,6 +241,17 @@ template <> struct Wide8<bf16_t> {
 template <> struct Wide8<float> {
   f32x4_t a, b;
   __device__ __forceinline__ void zero() { a = b = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ bool drop_nonfinite() {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool ba = !(fabsf(a[i]) < INFINITY), bb = !(fabsf(b[i]) < INFINITY);
+      bad |= ba | bb;
+      a[i] = ba ? 0.0f : a[i];
+      b[i] = bb ? 0.0f : b[i];
+    }
+    return bad;
+  }
   __device__ __forceinline__ void load(const float* p) {
     a = *reinterpret_cast<const f32x4_t*>(p);
     b = *reinterpret_cast<const f32x4_t*>(p + 4);
@@ -207,7 +264,11 @@ template <> struct Wide8<float> {
 
 // Mrows: rows of the output (tokens for kDx, experts for kDw); K: the
 // reduction length; k_per: its length per split (a multiple of 32).
-template <typename T, int MODE>
+// SPARSE (kDw): dl is zero outside each token's selected experts, and an expert's
+// row may see only its own tokens: 0 * x must stay 0 for an infinite or NaN x.
+// Such elements are left out of the matrix product and added afterwards to the
+// experts whose dl is not zero (they make those sums infinite or NaN in any order).
+template <typename T, int MODE, bool SPARSE = false>
 __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
     const float* __restrict__ dl, const T* __restrict__ B, const uint8_t* __restrict__ alive,
     int Mrows, int K, int k_per, int E, int d, int accumulate, T* __restrict__ dx, float* __restrict__ part,
@@ -221,6 +282,8 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
   const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
   const int k0 = blockIdx.z * k_per, k1 = min(K, k0 + k_per);
 
+  static_assert(!SPARSE || MODE == kDw, "dx reads every alive expert's row");
+  bool nonfinite = false;
   float ra[BM * KC / 256];
   Wide8<T> rb[KC * BN / 8 / 256];
   auto load = [&](int kb) {
@@ -254,6 +317,7 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
 #pragma unroll
     for (int i = 0; i < KC * BN / 8 / 256; ++i) {
       const int q = i * 256 + tid;
+      if constexpr (SPARSE) nonfinite |= rb[i].drop_nonfinite();
       rb[i].put(sB + (q / (BN / 8)) * LDB + (q % (BN / 8)) * 8);
     }
   };
@@ -312,6 +376,23 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
       }
   }
   if (sums_bias && m0 + tid < Mrows) part_b[(size_t)blockIdx.z * Mrows + m0 + tid] = bias;
+  if constexpr (SPARSE) {
+    // the elements left out, after the tile's stores (same workgroup, so the
+    // barrier orders them)
+    if (__syncthreads_or(nonfinite ? 1 : 0)) {
+      const int m1 = min(Mrows, m0 + BM);
+      for (int q = tid; q < (k1 - k0) * BN; q += 256) {
+        const int kk = k0 + q / BN, c = n0 + q % BN;
+        if (c >= d) continue;
+        const float v = widen(B[(size_t)kk * d + c]);
+        if (fabsf(v) < INFINITY) continue;
+        for (int m = m0; m < m1; ++m) {
+          const float w = dl[(size_t)kk * E + m];
+          if (w != 0.0f) atomicAdd(part + ((size_t)blockIdx.z * Mrows + m) * d + c, w * v);
+        }
+      }
+    }
+  }
 }
 
 // dW_r = sum of the splits' partial tiles in split order, db likewise.  One
@@ -353,7 +434,7 @@ inline DenseSplit dense_split(int T, int E, int d) {
   return {per > 0 ? (T + per - 1) / per : 0, per};
 }
 
-// Renormalised gates, weight gradient in two deterministic passes.
+// Renormalised gates of many experts, weight gradient in two deterministic passes.
 // Pass 1: one workgroup per 128-row segment of an expert's routed rows (the
 // row-tile table); the segment's (token, weight) pairs go to LDS first, then
 // every x row is read whole (each thread one 8-column vector, eight rows in
@@ -464,9 +545,18 @@ __global__ void fill_zero_kernel(float* __restrict__ p, size_t n) {
 
 }  // namespace
 
-// ws: dl; then, for renormalised gates, the segment table, partial rows and
-// sums; for full-softmax gates the splits' partial tiles and sums.
+// ws: dl by slot, dl by expert; then the segment table, partial rows and sums, or
+// the dense product's partial tiles and sums.
 inline int seg_max(int T, int k, int E) { return (int)(((int64_t)T * k + kSegRows - 1) / kSegRows) + E; }
+
+// Renormalised gates, dW_r: the dense product over all tokens and experts (dl is
+// zero outside the k selected ones) or the segment sums over the routed rows.  The
+// dense product's work grows with E in steps of its 64-expert tiles, the segments'
+// reads with k.  Whole weights-only call, dense / segments, d 2048, 8192 tokens:
+// 64 experts top-8 42 / 74 us, top-2 40 / 58, 16 experts top-2 33 / 60; 128 experts
+// top-8 64 / 72, top-2 64 / 58; 256 experts top-8 110 / 71, top-2 111 / 47.  1000
+// tokens of 64 experts, top-2, d 1024: 14 / 20.
+inline bool renorm_dw_dense(int k, int E) { return E <= 64 || E <= 16 * k; }
 
 size_t route_bwd_ws_bytes(int T, int k, int E, int d) {
   const int m = seg_max(T, k, E);
@@ -474,10 +564,28 @@ size_t route_bwd_ws_bytes(int T, int k, int E, int d) {
                      align_up((size_t)m * sizeof(float), 256);
   const size_t n = dense_split(T, E, d).n;
   const size_t dense = align_up(n * E * d * sizeof(float), 256) + align_up(n * E * sizeof(float), 256);
-  return align_up((size_t)T * (k > E ? k : E) * sizeof(float), 256) + (seg > dense ? seg : dense);
+  return align_up((size_t)T * k * sizeof(float), 256) + align_up((size_t)T * E * sizeof(float), 256) +
+         (seg > dense ? seg : dense);
 }
 
 namespace {
+
+// dW_r (and db) from the dense dl [T, E]
+template <typename T, bool SPARSE>
+void launch_dense_dw(const float* dl, const T* x, int T_, int E, int d, char* base,
+                     float* dw_router, float* dbias, hipStream_t s) {
+  const DenseSplit sp = dense_split(T_, E, d);
+  float* part = reinterpret_cast<float*>(base);
+  float* part_b = reinterpret_cast<float*>(base + align_up((size_t)sp.n * E * d * sizeof(float), 256));
+  hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDw, SPARSE>),
+                     dim3((unsigned)((E + kDenseBM - 1) / kDenseBM),
+                          (unsigned)((d + kDenseBN - 1) / kDenseBN), (unsigned)sp.n),
+                     dim3(256), 0, s, dl, x, nullptr, E, T_, sp.per, E, d, 0,
+                     static_cast<T*>(nullptr), part, dbias ? part_b : nullptr);
+  const size_t n = (size_t)E * d;  // >= E
+  hipLaunchKernelGGL(route_bwd_dense_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256),
+                     0, s, part, part_b, sp.n, E, d, dw_router, dbias);
+}
 
 template <typename T>
 hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const float* gate,
@@ -486,36 +594,31 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
                               int T_, int d, int E, int k, int renorm, float* dlogits,
                               float* dw_router, float* dbias, T* dx, int accumulate_dx, void* ws,
                               hipStream_t s) {
-  float* dl = static_cast<float*>(ws);
-  char* base = static_cast<char*>(ws) + align_up((size_t)T_ * (k > E ? k : E) * sizeof(float), 256);
+  float* dl = static_cast<float*>(ws);  // [T, k]
+  float* dl_dense = reinterpret_cast<float*>(static_cast<char*>(ws) +
+                                             align_up((size_t)T_ * k * sizeof(float), 256));
+  char* base = reinterpret_cast<char*>(dl_dense) + align_up((size_t)T_ * E * sizeof(float), 256);
   if (!renorm) {
     hipLaunchKernelGGL(route_bwd_dl_full_kernel, dim3((T_ + 3) / 4), dim3(kDlThreads), 0, s, dgate,
-                       idx, gate, logits, alive, T_, E, k, dl, dlogits);
-    const unsigned gn = (unsigned)((d + kDenseBN - 1) / kDenseBN);
+                       idx, gate, logits, alive, T_, E, k, dl_dense, dlogits);
     if (dx)
       hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDx>),
-                         dim3((unsigned)((T_ + kDenseBM - 1) / kDenseBM), gn), dim3(256), 0, s, dl,
-                         w_router, alive, T_, E, E, E, d, accumulate_dx, dx, nullptr, nullptr);
-    if (dw_router) {
-      const DenseSplit sp = dense_split(T_, E, d);
-      float* part = reinterpret_cast<float*>(base);
-      float* part_b = reinterpret_cast<float*>(base + align_up((size_t)sp.n * E * d * sizeof(float), 256));
-      hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDw>),
-                         dim3((unsigned)((E + kDenseBM - 1) / kDenseBM), gn, (unsigned)sp.n),
-                         dim3(256), 0, s, dl, x, nullptr, E, T_, sp.per, E, d, 0, static_cast<T*>(nullptr),
-                         part, dbias ? part_b : nullptr);
-      const size_t n = (size_t)E * d;  // >= E
-      hipLaunchKernelGGL(route_bwd_dense_reduce_kernel, dim3((unsigned)((n + 255) / 256)),
-                         dim3(256), 0, s, part, part_b, sp.n, E, d, dw_router, dbias);
-    }
+                         dim3((unsigned)((T_ + kDenseBM - 1) / kDenseBM),
+                              (unsigned)((d + kDenseBN - 1) / kDenseBN)),
+                         dim3(256), 0, s, dl_dense, w_router, alive, T_, E, E, E, d, accumulate_dx,
+                         dx, nullptr, nullptr);
+    if (dw_router) launch_dense_dw<T, false>(dl_dense, x, T_, E, d, base, dw_router, dbias, s);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL(route_bwd_dl_kernel, dim3((T_ + kDlThreads - 1) / kDlThreads),
-                     dim3(kDlThreads), 0, s, dgate, idx, gate, T_, E, k, dl, dlogits);
+  const bool dense = dw_router && renorm_dw_dense(k, E);
+  hipLaunchKernelGGL(route_bwd_dl_kernel, dim3((T_ + 3) / 4), dim3(kDlThreads), 0, s, dgate, idx,
+                     gate, T_, E, k, dl, dense ? dl_dense : nullptr, dlogits);
   if (dx)
     hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,
                        w_router, idx, dl, T_, k, d, accumulate_dx, dx);
-  if (dw_router) {
+  if (dense) {
+    launch_dense_dw<T, true>(dl_dense, x, T_, E, d, base, dw_router, dbias, s);
+  } else if (dw_router) {
     // segment table of the routed rows (pass 1 + 2)
     const int m = seg_max(T_, k, E);
     TableWs tw = carve_table(base, m);

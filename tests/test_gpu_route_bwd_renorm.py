@@ -1,0 +1,72 @@
+"""The router's weight gradients of renormalised gates, dense product and
+segment sums (the choice falls between E = 64 or 16 k and more), against plain
+float64, at the edges of their tiles; an infinite token touches only the rows of
+the experts it is routed to."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2601_14327_amd as laep
+from _gpu import TOL_F32, case, host, rownorm_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(T, E, k, d, dtype, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((T, d), generator=g, device="cuda").to(dtype)
+    wr = (0.05 * torch.randn((E, d), generator=g, device="cuda")).to(dtype)
+    idx, gate = laep.moe_route(x, wr, k)[:2]
+    _, off, _, src = laep.moe_expert_counts(idx, E, want_row_src=True)
+    dg = torch.randn((T, k), generator=g, device="cuda")
+    return x, wr, idx, gate, off, src, dg
+
+
+def _dw(x, wr, idx, gate, off, src, dg):
+    _, dw, db, dl = laep.moe_route_bwd(dg, idx, gate, x, wr, offsets=off, row_src=src, data=False,
+                                       want_dbias=True, want_dlogits=True)
+    torch.cuda.synchronize()
+    return dw, db, dl
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,E,k,d", [
+    (1, 8, 2, 64),          # one token
+    (65, 64, 8, 136),       # one token past a split's two steps, d % 128 = 8
+    (300, 65, 5, 128),      # dense by 16 k, one expert past a tile
+    (300, 128, 8, 264),     # dense, two expert tiles
+    (300, 130, 8, 264),     # segments
+    (257, 65, 1, 128),      # segments
+    (40, 200, 100, 64),     # more than 64 slots, dense
+])
+def test_weights(T, E, k, d, dtype):
+    case(f"router renorm weights T={T} E={E} k={k} d={d} {dtype}")
+    x, wr, idx, gate, off, src, dg = a = _inputs(T, E, k, d, dtype, 3 * T + E)
+    dw, db, dl = _dw(*a)
+    g, q = gate.double(), dg.double()
+    dls = g * (q - (g * q).sum(1, keepdim=True))
+    full = torch.zeros((T, E), dtype=torch.float64, device="cuda").scatter_(1, idx.long(), dls)
+    # fp32 sums of at most 300 terms
+    cond = (full.abs().t() @ x.double().abs()).clamp_min(1e-30)
+    assert ((dw.double() - full.t() @ x.double()).abs() <= TOL_F32 * cond).all()
+    assert rownorm_err(host(dl), host(full)) <= TOL_F32
+    assert ((db.double() - full.sum(0)).abs() <= TOL_F32 * full.abs().sum(0) + 1e-30).all()
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("E,k", [(64, 4), (130, 4)])
+def test_infinite_token(E, k, bad):
+    T, d = 200, 136
+    case(f"router renorm weights, token with {bad} E={E}")
+    x, wr, idx, gate, off, src, dg = _inputs(T, E, k, d, torch.bfloat16, E)
+    t, c = 131, 77
+    xz, xb = x.clone(), x.clone()
+    xz[t, c], xb[t, c] = 0.0, bad
+    ref = _dw(xz, wr, idx, gate, off, src, dg)[0]
+    got = _dw(xb, wr, idx, gate, off, src, dg)[0]
+    hit = torch.zeros(E, dtype=torch.bool, device="cuda")
+    hit[idx[t].long()] = True
+    assert not torch.isfinite(got[hit, c]).any()
+    ok = torch.ones_like(ref, dtype=torch.bool)
+    ok[hit, c] = False
+    assert torch.equal(got[ok], ref[ok])
