@@ -23,20 +23,22 @@
 // measured with LDS-DMA), so whole lines double the bytes per request against
 // the 64-byte half lines of 32-wide k-steps.  One operand's k-step is a 32 KB
 // "half"; the LDS is a ring of five halves (A0 B0 A1 B1 A2 | B2 A3 ...), so
-// while step i computes, the B half of step i+1 and the A half of step i+2
-// are in flight: A has almost two k-steps (2048 MFMA cycles per SIMD each) to
-// land and B one.
+// while step i computes, both halves of step i+1 are in flight, and from its last
+// sub-steps on the A half of step i+2: every half has about one k-step (2048 MFMA
+// cycles per SIMD) to land.
 //
 // The order of issue inside a k-step is written out MFMA by MFMA: one fragment
-// read of the next k16 sub-step beside each MFMA, and the eight copies of a wave
-// one per two MFMAs in the two sub-steps after the step boundary.  Issued in one
-// burst after the boundary, the 64 copies of the eight waves queue behind each
-// other in the address unit (16 clocks each) ahead of the MFMAs that follow them.
-// Layer forward before / after: 8192 tokens top-8, d 2048, d_ff 1024, 888 / 868 us;
-// after pruning 853 / 821; 32768 rows, 16 experts, d 4096, d_ff 2048, 1528 / 1486.
-// One copy per four MFMAs over the whole k-step is slower (895 and 1545 us): B
-// then has less than a k-step to land.  Four waves of 128 x 128, a third fewer
-// fragment reads, run the k-loop no faster, and their epilogue spills.
+// read of the next k16 sub-step beside each MFMA, the wave's four copies of B one
+// per MFMA right after the step boundary, those of A one per two MFMAs in the
+// sub-step before it.  Issued in one burst after the boundary, the 64 copies of
+// the eight waves queue behind each other in the address unit (16 clocks each)
+// ahead of the MFMAs that follow them.  Layer forward, us: burst / B and A one per
+// two MFMAs after the boundary / as it is: 8192 tokens top-8, d 2048, d_ff 1024
+// 888 / 850 / 831; after pruning 853 / 821 / 814; 32768 rows, 16 experts, d 4096,
+// d_ff 2048 1528 / 1478 / 1461.  Others: one copy per four MFMAs over the whole
+// k-step 895 and 1545 (first and last); one per MFMA, all after the boundary, 877
+// and 1503.  Four waves of 128 x 128, a third fewer fragment reads, run the k-loop
+// no faster, and their epilogue spills.
 #include <type_traits>
 
 #include "common.hpp"
@@ -328,12 +330,13 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
       else fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_off[i] ^ (s << 5)));
     };
     // One k16 sub-step: the MFMAs on (fa, fb), and beside them, in this order,
-    // the fragment reads (ga, gb) of the next sub-step and the NV copies of
-    // half h.
+    // the fragment reads (ga, gb) of the next sub-step and the copies of half h,
+    // one every `every` MFMAs (0: none).
     auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
-                        int s, u32x4_t* ga, u32x4_t* gb, auto nv_tag, int h) {
-      constexpr int NV = decltype(nv_tag)::value;
-      constexpr int MOST = NMM > NRD ? (NMM > 2 * NV ? NMM : 2 * NV) : (NRD > 2 * NV ? NRD : 2 * NV);
+                        int s, u32x4_t* ga, u32x4_t* gb, auto every_tag, int h) {
+      constexpr int EVERY = decltype(every_tag)::value;
+      constexpr int SLOTS = EVERY * NH, WORK = NMM > NRD ? NMM : NRD;
+      constexpr int MOST = WORK > SLOTS ? WORK : SLOTS;
 #pragma unroll
       for (int n = 0; n < MOST; ++n) {
         if (n < NMM) {
@@ -347,14 +350,15 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
           read_frag(sa, sb, s, ga, gb, n);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        if (n < 2 * NV && (n & 1)) {
-          issue_chunk(h, n / 2);
+        if (n < SLOTS && n % EVERY == EVERY - 1) {
+          issue_chunk(h, n / EVERY);
           __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
         }
       }
     };
-    using Copies = std::integral_constant<int, NH>;
-    using NoCopies = std::integral_constant<int, 0>;
+    using Every0 = std::integral_constant<int, 0>;
+    using Every1 = std::integral_constant<int, 1>;
+    using Every2 = std::integral_constant<int, 2>;
 
     // prologue: halves 0 .. 3 in flight, step 0 (halves 0, 1) landed
 #pragma unroll
@@ -369,19 +373,19 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
     for (int kt = 0; kt < nk; ++kt) {
       const char* sa = smem + ia * HALF;
       const char* sb = smem + ib * HALF;
-      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, Copies{}, 2 * kt + 4);
-      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, NoCopies{}, 0);
-      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, NoCopies{}, 0);
+      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, Every0{}, 0);
+      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, Every0{}, 0);
+      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, Every2{}, 2 * kt + 4);
       // step boundary: this thread's reads of step kt are in registers and its
       // loads of step kt+1 have landed (only the A half of step kt+2 may still
       // be in flight); past the barrier the same holds for every thread, so the
-      // two halves of step kt are free: they receive B of kt+2 now and A of
-      // kt+3 in the next iteration.
+      // two halves of step kt are free: its A slot receives B of kt+2 now, its B
+      // slot A of kt+3 in the next iteration.
       wait_vmcnt_lgkm0<NH>();
       __builtin_amdgcn_s_barrier();
       ia = ia + 2 >= NSLOT ? ia + 2 - NSLOT : ia + 2;
       ib = ib + 2 >= NSLOT ? ib + 2 - NSLOT : ib + 2;
-      sub_step(fa1, fb1, smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0, Copies{}, 2 * kt + 5);
+      sub_step(fa1, fb1, smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0, Every1{}, 2 * kt + 5);
     }
   };
   // wave-uniform count of this wave's 32-row blocks that hold expert rows
@@ -698,12 +702,13 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
       else fa[i] = *reinterpret_cast<const u32x4_t*>(sa + (a_off[i] ^ (s << 5)));
     };
     // One k16 sub-step: the MFMAs on (fa, fb), and beside them, in this order,
-    // the fragment reads (ga, gb) of the next sub-step and the NV copies of
-    // half h.
+    // the fragment reads (ga, gb) of the next sub-step and the copies of half h,
+    // one every `every` MFMAs (0: none).
     auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
-                        int s, u32x4_t* ga, u32x4_t* gb, auto nv_tag, int h) {
-      constexpr int NV = decltype(nv_tag)::value;
-      constexpr int MOST = NMM > NRD ? (NMM > 2 * NV ? NMM : 2 * NV) : (NRD > 2 * NV ? NRD : 2 * NV);
+                        int s, u32x4_t* ga, u32x4_t* gb, auto every_tag, int h) {
+      constexpr int EVERY = decltype(every_tag)::value;
+      constexpr int SLOTS = EVERY * NH, WORK = NMM > NRD ? NMM : NRD;
+      constexpr int MOST = WORK > SLOTS ? WORK : SLOTS;
 #pragma unroll
       for (int n = 0; n < MOST; ++n) {
         if (n < NMM) {
@@ -717,14 +722,15 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
           read_frag(sa, sb, s, ga, gb, n);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        if (n < 2 * NV && (n & 1)) {
-          issue_chunk(h, n / 2);
+        if (n < SLOTS && n % EVERY == EVERY - 1) {
+          issue_chunk(h, n / EVERY);
           __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
         }
       }
     };
-    using Copies = std::integral_constant<int, NH>;
-    using NoCopies = std::integral_constant<int, 0>;
+    using Every0 = std::integral_constant<int, 0>;
+    using Every1 = std::integral_constant<int, 1>;
+    using Every2 = std::integral_constant<int, 2>;
 
     // the fragment offsets are made opaque here, so the offsets each
     // instantiation derives from them are not hoisted out of the tile loop
@@ -744,14 +750,14 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
     for (int kt = 0; kt < nk; ++kt) {
       const char* sa = smem + ia * HALF;
       const char* sb = smem + ib * HALF;
-      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, Copies{}, 2 * kt + 4);
-      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, NoCopies{}, 0);
-      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, NoCopies{}, 0);
+      sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, Every0{}, 0);
+      sub_step(fa1, fb1, sa, sb, 2, fa0, fb0, Every0{}, 0);
+      sub_step(fa0, fb0, sa, sb, 3, fa1, fb1, Every2{}, 2 * kt + 4);
       wait_vmcnt_lgkm0<NH>();
       __builtin_amdgcn_s_barrier();
       ia = ia + 2 >= NSLOT ? ia + 2 - NSLOT : ia + 2;
       ib = ib + 2 >= NSLOT ? ib + 2 - NSLOT : ib + 2;
-      sub_step(fa1, fb1, smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0, Copies{}, 2 * kt + 5);
+      sub_step(fa1, fb1, smem + ia * HALF, smem + ib * HALF, 0, fa0, fb0, Every1{}, 2 * kt + 5);
     }
   };
 

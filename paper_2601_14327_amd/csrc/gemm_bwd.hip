@@ -28,13 +28,23 @@
 // weight gradients) is far larger than the caches (measured 3 % faster on the
 // backward call).
 //
+// The order of issue inside a k-step is written out MFMA by MFMA, as in the
+// forward: one fragment of the next k16 sub-step beside each MFMA, the copies of B
+// one per MFMA right after the step boundary, those of A one per two MFMAs before
+// it.  Left to the compiler, the fragment reads came in blocks that were
+// waited for as blocks and the eight copies in a burst ahead of the MFMAs; the
+// row / slots_k divisions of the gathered rows are one high multiply and a
+// correction (a 32-bit division is about 25 instructions, four per k-step).
+// Training steps, before / after: 8192 tokens top-8, d 2048, d_ff 1024, 3242 /
+// 3119 us; 32768 rows, 16 experts, d 4096, d_ff 2048, 5531 / 5298 us; 1000 tokens
+// top-2, d 1024, d_ff 2048, 796 / 726 us.
+//
 // Gathered X (the dispatch folded into the weight gradient): dW_gu = dA^T X
 // can read X's routed row r straight from token row row_src[r] / k of x, so
 // x_perm is never written.  The k-rows of a k-step are then different token
 // rows at every step: each thread loads the row_src entries of its 4 k-rows
-// one k-step ahead, issued before that iteration's LDS-DMA halves, so the
-// in-order vmcnt waits of the ring still cover them.  Rows past the expert's
-// end get an offset beyond x's buffer range and read as zeros.
+// one k-step ahead, beside the copies of the step before.  Rows past the
+// expert's end get an offset beyond x's buffer range and read as zeros.
 //
 // dY formed on load (the gate scaling of the combine backward folded into
 // data-gradient 1 and dW_d): their A operand dY = round(g * dout) is read from
@@ -42,10 +52,10 @@
 // gate[row_src[r]], one fp32 product rounded to bf16, exactly as
 // moe_combine_bwd forms dy_perm), so dy_perm is never written.  The A halves
 // are LDS-DMA'd from dout's token rows through row_src as usual (a gather, as
-// in the forward), and each thread scales its own chunks in place just before
-// the step boundary at which that half has landed: the ring's prefetch depth
-// is unchanged, and the transform's LDS round trip overlaps the last
-// sub-step's MFMAs.
+// in the forward), and each
+// thread scales its own chunks in place beside the MFMAs of the two sub-steps
+// before the boundary that publishes them, once the copies of that half have
+// landed.
 #include <type_traits>
 
 #include "gemm_common.hpp"
@@ -138,8 +148,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
   static_assert(BM == 256 && BN == 256 && NT == 512, "ring halves are 256 x 64 / 64 x 256");
   static_assert(NWM == 2, "the staged epilogues process one wave row per pass");
   constexpr int PITCH16 = BN * 2 + 16;   // bf16 staging pitch
-  constexpr int PITCH32 = BN * 4 + 16;   // fp32 staging pitch
-  constexpr int EPI_BYTES = (EPI == EPI_WGRAD) ? 128 * PITCH32 : BM * PITCH16;
+  constexpr int EPI_BYTES = (EPI == EPI_WGRAD) ? 0 : BM * PITCH16;
   constexpr int RING = kRingSlots * kRingHalf;
   constexpr int SMEM = RING > EPI_BYTES ? RING : EPI_BYTES;
   __shared__ __attribute__((aligned(1024))) char smem[SMEM];
@@ -398,9 +407,14 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
       for (int n = 0; n < 8; ++n) {
         if (n < NMM) {
           const int i = n / TN, j = n % TN;
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              __builtin_bit_cast(bf16x8_t, fb[j]), __builtin_bit_cast(bf16x8_t, fa[i]), acc[i][j],
-              0, 0, 0);
+          // weight gradients: a lane owns one output column and 4 consecutive rows
+          // per register quad; data gradients (operands swapped): one row and 4
+          // consecutive columns
+          const u32x4_t lhs = EPI == EPI_WGRAD ? fa[i] : fb[j];
+          const u32x4_t rhs = EPI == EPI_WGRAD ? fb[j] : fa[i];
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, lhs),
+                                                              __builtin_bit_cast(bf16x8_t, rhs),
+                                                              acc[i][j], 0, 0, 0);
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
         }
         if (n < NRD) read_frag(sa, sb, s, ga, gb, n);
@@ -480,8 +494,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
     for (int kt = 0; kt < nk; ++kt) {
       const char* sa = smem + ia * kRingHalf;
       const char* sb = smem + ib * kRingHalf;
-      // A of step kt+2, one copy per two MFMAs (dW_d with dY on load: and the
-      // row ids of step kt+3)
+      // A of step kt+2, one copy per two MFMAs, just before the boundary; with dY on
+      // load, which scales it ahead of use, here (dW_d: and the row ids of kt+3)
       sub_step(fa0, fb0, sa, sb, 1, fa1, fb1, [&](int n) {
         if constexpr (A_DY && A_TR) {
           if (n & 1) {
@@ -490,7 +504,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
             src_next[n / 2] = row_id(kt + 3, ady_kr[n / 2]);
           }
           one_vmem();
-        } else {
+        } else if constexpr (A_DY) {
           if (n & 1) {
             issue_chunk(2 * kt + 4, n / 2);
             one_vmem();
@@ -519,6 +533,11 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
             __builtin_amdgcn_sched_group_barrier(0x002, 20, 0);
             __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
           }
+        } else {
+          if (n & 1) {
+            issue_chunk(2 * kt + 4, n / 2);
+            one_vmem();
+          }
         }
       });
       // step boundary: this thread's reads of step kt are in registers and its
@@ -534,17 +553,15 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
       ib = ib + 2 >= kRingSlots ? ib + 2 - kRingSlots : ib + 2;
       sub_step(fa1, fb1, smem + ia * kRingHalf, smem + ib * kRingHalf, 0, fa0, fb0, [&](int n) {
         if constexpr (B_GATHER) {
-          if (n & 1) issue_b_gathered(kt + 2, n / 2, src[n / 2]);
-          else src_next[n / 2] = row_id(kt + 3, b_kr[n / 2]);
+          if (n < NH) issue_b_gathered(kt + 2, n, src[n]);
+          else src_next[n - NH] = row_id(kt + 3, b_kr[n - NH]);
           one_vmem();
-        } else {
-          if (n & 1) {
-            issue_chunk(2 * kt + 5, n / 2);
-            one_vmem();
-          } else if constexpr (A_DY && A_TR) {
-            g[n / 2] = p.gate[src[n / 2]];
-            one_vmem();
-          }
+        } else if (n < NH) {
+          issue_chunk(2 * kt + 5, n);
+          one_vmem();
+        } else if constexpr (A_DY && A_TR) {
+          g[n - NH] = p.gate[src[n - NH]];
+          one_vmem();
         }
       });
       if constexpr (B_GATHER || (A_DY && A_TR)) {
@@ -570,57 +587,51 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
     }
   }
 
-  // ---- epilogues (staged through LDS) -------------------------------------------
-  wait_lgkm0();
-  __builtin_amdgcn_s_barrier();
+  // ---- epilogues ----------------------------------------------------------------
   const int lrow = lane & 31;
   const int lcol = (lane >> 5) * 4;
 
   if (EPI == EPI_WGRAD) {
-    // fp32 dW tile, 128 rows (one wave row) per pass
-    float* W = p.wout + (long long)te.phys * p.strideW;
-    const int ncols = min(BN, p.N - nt * BN);
-    for (int pass = 0; pass < 2; ++pass) {
-      if (wm == pass) {
+    // fp32 dW straight from the accumulators: each store instruction writes one
+    // whole 128-byte line of two rows (a half-wave's 32 columns each), so nothing
+    // is staged and no wave waits for another; the stores drain behind the next
+    // workgroup's first loads.  (Staged through LDS for 16-byte stores, two passes
+    // of 128 rows and four barriers, the epilogue took 8 of a dW_gu tile's 48 us.)
+    float* W = p.wout + (long long)te.phys * p.strideW +
+               (long long)(mt * BM + wm * WTM) * p.N + nt * BN + wn * WTN;
+    const __amdgpu_buffer_rsrc_t w_rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(W, 0, -1, kBufferFlags);
+    const int voff = (lcol * p.N + lrow) * 4;
+    const int row_bytes = p.N * 4;
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
+      if (mt * BM + wm * WTM + i * 32 >= p.Mw) break;  // Mw, N: multiples of 64
 #pragma unroll
-          for (int j = 0; j < TN; ++j)
+      for (int j = 0; j < TN; ++j) {
+        if (nt * BN + wn * WTN + j * 32 >= p.N) break;
+        const int at = voff + j * 128;
+        float v[16];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              const int r = i * 32 + lrow;
-              const int c = wn * WTN + j * 32 + q * 8 + lcol;
-              f32x4_t v = {acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2],
-                           acc[i][j][q * 4 + 3]};
-              *reinterpret_cast<f32x4_t*>(smem + r * PITCH32 + c * 4) = v;
-            }
-      }
-      wait_lgkm0();
-      __builtin_amdgcn_s_barrier();
-      // fixed trip count (BN columns): every LDS read of a thread before one wait
-      constexpr int CPR = BN / 4, ITERS = 128 * CPR / NT;
-      const int cpr = ncols / 4;
-      f32x4_t v[ITERS];
+        for (int r = 0; r < 16; ++r) v[r] = acc[i][j][r];
+        if (p.accumulate) {
+          float o[16];
 #pragma unroll
-      for (int it = 0; it < ITERS; ++it) {
-        const int c = it * NT + tid;
-        v[it] = *reinterpret_cast<const f32x4_t*>(smem + (c / CPR) * PITCH32 + (c % CPR) * 16);
-      }
+          for (int r = 0; r < 16; ++r)
+            o[r] = __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
+                w_rsrc, at, (i * 32 + (r >> 2) * 8 + (r & 3)) * row_bytes, kDmaStream));
 #pragma unroll
-      for (int it = 0; it < ITERS; ++it) {
-        const int c = it * NT + tid;
-        const int r = c / CPR, cc = c % CPR;
-        const int row = mt * BM + pass * 128 + r;
-        if (row < p.Mw && cc < cpr) {
-          f32x4_t* dst = reinterpret_cast<f32x4_t*>(W + (long long)row * p.N + nt * BN + cc * 4);
-          if (p.accumulate) v[it] += *dst;
-          st_stream(dst, v[it]);
+          for (int r = 0; r < 16; ++r) v[r] += o[r];
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v[r]), w_rsrc, at,
+                                                (i * 32 + (r >> 2) * 8 + (r & 3)) * row_bytes,
+                                                kDmaStream);
       }
-      wait_lgkm0();
-      __builtin_amdgcn_s_barrier();
     }
-  } else {  // EPI_STORE (bf16 rows: dH, dX)
+  } else {  // EPI_STORE (bf16 rows: dH, dX), staged through LDS
+    wait_lgkm0();
+    __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int r = wm * WTM + i * 32 + lrow;
@@ -758,10 +769,9 @@ hipError_t launch_ffn_bwd_bf16(const void* dy, const void* x_perm, const void* a
   const int max_ragged = ceil_div(R, kBwdBM) + E;
   TableWs tr = carve_table(tables, max_ragged);
   TableWs te = carve_table(tables + table_bytes(max_ragged), E);
-  hipLaunchKernelGGL(build_table_kernel, dim3(1), dim3(kTableThreads), 0, s, offsets, expert_map,
-                     E, kBwdBM, 0, max_ragged, tr.n_entries, tr.table);
-  hipLaunchKernelGGL(build_table_kernel, dim3(1), dim3(kTableThreads), 0, s, offsets, expert_map,
-                     E, kBwdBM, 1, E, te.n_entries, te.table);
+  hipLaunchKernelGGL(build_tables_bwd_kernel, dim3(2), dim3(kTableThreads), 0, s, offsets,
+                     expert_map, E, kBwdBM, max_ragged, tr.n_entries, tr.table, E, te.n_entries,
+                     te.table);
 
   const int group = kBwdTileGroup;
   // weight gradients: dW_d[p] [d, f] = dY^T H over the expert's rows (H: the

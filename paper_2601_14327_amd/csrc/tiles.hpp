@@ -43,7 +43,7 @@ __device__ __forceinline__ int block_excl_scan_256(int v, int* s_tmp) {
 
 // mode 0: one entry per BM-row tile of every expert with rows (ragged M)
 // mode 1: one entry per expert that has a weight slot, longest first (wgrad)
-__global__ __launch_bounds__(kTableThreads) void build_table_kernel(
+__device__ __forceinline__ void build_table(
     const int32_t* __restrict__ offsets, const int32_t* __restrict__ expert_map, int E, int BM,
     int mode, int max_entries, int* __restrict__ n_entries, TileEntry* __restrict__ table) {
   __shared__ int s_rows[kTableThreads];
@@ -100,6 +100,23 @@ __global__ __launch_bounds__(kTableThreads) void build_table_kernel(
     int tot = block_excl_scan_256(cnt, s_tmp) + cnt;
     if (e == kTableThreads - 1) *n_entries = min(tot, max_entries);
   }
+}
+
+__global__ __launch_bounds__(kTableThreads) void build_table_kernel(
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ expert_map, int E, int BM,
+    int mode, int max_entries, int* __restrict__ n_entries, TileEntry* __restrict__ table) {
+  build_table(offsets, expert_map, E, BM, mode, max_entries, n_entries, table);
+}
+
+// the backward's two tables (row tiles, experts), one workgroup each
+__global__ __launch_bounds__(kTableThreads) void build_tables_bwd_kernel(
+    const int32_t* __restrict__ offsets, const int32_t* __restrict__ expert_map, int E, int BM,
+    int max_ragged, int* __restrict__ n_ragged, TileEntry* __restrict__ ragged, int max_experts,
+    int* __restrict__ n_experts, TileEntry* __restrict__ experts) {
+  if (blockIdx.x == 0)
+    build_table(offsets, expert_map, E, BM, 0, max_ragged, n_ragged, ragged);
+  else
+    build_table(offsets, expert_map, E, BM, 1, max_experts, n_experts, experts);
 }
 
 // Per-tile lists of two row-tile products (one launch): every (row tile,
