@@ -335,6 +335,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
     auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
                         int s, u32x4_t* ga, u32x4_t* gb, auto every_tag, int h) {
       constexpr int EVERY = decltype(every_tag)::value;
+      static_assert(EVERY >= 0 && EVERY <= 2, "none, one per MFMA or one per two");
       constexpr int SLOTS = EVERY * NH, WORK = NMM > NRD ? NMM : NRD;
       constexpr int MOST = WORK > SLOTS ? WORK : SLOTS;
 #pragma unroll
@@ -350,8 +351,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_ring_kernel(GemmParams
           read_frag(sa, sb, s, ga, gb, n);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        if (n < SLOTS && n % EVERY == EVERY - 1) {
-          issue_chunk(h, n / EVERY);
+        if (n < SLOTS && (EVERY != 2 || n % 2 == 1)) {
+          issue_chunk(h, EVERY == 2 ? n / 2 : n);
           __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
         }
       }
@@ -707,6 +708,7 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
     auto sub_step = [&](const u32x4_t* fa, const u32x4_t* fb, const char* sa, const char* sb,
                         int s, u32x4_t* ga, u32x4_t* gb, auto every_tag, int h) {
       constexpr int EVERY = decltype(every_tag)::value;
+      static_assert(EVERY >= 0 && EVERY <= 2, "none, one per MFMA or one per two");
       constexpr int SLOTS = EVERY * NH, WORK = NMM > NRD ? NMM : NRD;
       constexpr int MOST = WORK > SLOTS ? WORK : SLOTS;
 #pragma unroll
@@ -722,8 +724,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
           read_frag(sa, sb, s, ga, gb, n);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
         }
-        if (n < SLOTS && n % EVERY == EVERY - 1) {
-          issue_chunk(h, n / EVERY);
+        if (n < SLOTS && (EVERY != 2 || n % 2 == 1)) {
+          issue_chunk(h, EVERY == 2 ? n / 2 : n);
           __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
         }
       }

@@ -35,9 +35,11 @@
 // waited for as blocks and the eight copies in a burst ahead of the MFMAs; the
 // row / slots_k divisions of the gathered rows are one high multiply and a
 // correction (a 32-bit division is about 25 instructions, four per k-step).
-// Training steps, before / after: 8192 tokens top-8, d 2048, d_ff 1024, 3242 /
-// 3119 us; 32768 rows, 16 experts, d 4096, d_ff 2048, 5531 / 5298 us; 1000 tokens
-// top-2, d 1024, d_ff 2048, 796 / 726 us.
+// Training steps, us, the compiler's order / A and B one copy per two MFMAs after
+// the boundary / as it is (the last with dY written once): 8192 tokens top-8,
+// d 2048, d_ff 1024, 3242 / 3027 / 2935; 32768 rows, 16 experts, d 4096, d_ff 2048,
+// 5531 / 5072 / 4945; 1000 tokens top-2, d 1024, d_ff 2048, 796 / 680 / 680.  The
+// call that forms dY on load: 2165 -> 1969 at the first.
 //
 // Gathered X (the dispatch folded into the weight gradient): dW_gu = dA^T X
 // can read X's routed row r straight from token row row_src[r] / k of x, so
@@ -290,17 +292,21 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
   // k-row kr of step ks, any entry of the expert's rows past its end (the
   // validity is applied at use), and the copy of one chunk through it: rows
   // past the end get an offset beyond the operand's buffer range and read as
-  // zeros.  Branch-free.
+  // zeros.  Branch-free (a branch would end the block the order is written in).
+  auto past_end = [&](int r) { return (uint32_t)~((r - kext) >> 31) & 0x80000000u; };
   auto row_id = [&](int ks, int kr) {
     const int r = ks * 64 + kr;
-    return (uint32_t)p.row_src[te.row0 + (r < kext ? r : 0)];
+    return (uint32_t)p.row_src[te.row0 + (r & ((r - kext) >> 31))];
   };
-  auto token_row = [&](uint32_t src) {  // src / slots_k
+  // src / slots_k; the id is made opaque at its use, or its wait and the arithmetic
+  // on it move up to just behind the load
+  auto token_row = [&](uint32_t src) {
+    asm volatile("" : "+v"(src));
     return div_slots(src, (uint32_t)p.slots_k, p.slots_magic);
   };
   auto issue_b_gathered = [&](int ks, int i, uint32_t src) {
-    const uint32_t v = ks * 64 + b_kr[i] < kext
-                           ? token_row(src) * (uint32_t)p.ldb * 2u + b_cb[i] : 0x80000000u;
+    const uint32_t v = (token_row(src) * (uint32_t)p.ldb * 2u + b_cb[i]) |
+                       past_end(ks * 64 + b_kr[i]);
     dma_half<1, NT>(smem + ((2 * ks + 1) % kRingSlots) * kRingHalf + i * NT * 16, b_tile,
                     p.b_extent, &v, wave);
   };
@@ -324,8 +330,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
     }
   }
   auto issue_a_gathered = [&](int ks, int i, uint32_t src) {
-    const uint32_t v = ks * 64 + ady_kr[i] < kext
-                           ? token_row(src) * (uint32_t)p.lda * 2u + ady_cb[i] : 0x80000000u;
+    const uint32_t v = (token_row(src) * (uint32_t)p.lda * 2u + ady_cb[i]) |
+                       past_end(ks * 64 + ady_kr[i]);
     dma_half<1, NT>(smem + ((2 * ks) % kRingSlots) * kRingHalf + i * NT * 16, a_tile, p.a_extent,
                     &v, wave);
   };
@@ -419,6 +425,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
         }
         if (n < NRD) read_frag(sa, sb, s, ga, gb, n);
         beside(n);
+        // dY on load: too much arithmetic for the group solver, the order as written
+        if constexpr (A_DY) __builtin_amdgcn_sched_barrier(0);
       }
     };
     static_assert(NMM <= 8 && NRD <= 8 && NH == 4, "a sub-step's eight slots");
@@ -530,7 +538,6 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
         if constexpr (A_DY) {
           if (n & 1) {
             *ady_chunk(kt + 1, n / 2) = scale_bf16x8(dy[n / 2], g[n / 2]);
-            __builtin_amdgcn_sched_group_barrier(0x002, 20, 0);
             __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
           }
         } else {
