@@ -68,9 +68,12 @@ __device__ __forceinline__ void build_table(
     start = block_excl_scan_256(cnt, s_tmp);
   } else {  // rank by rows descending, then index
     start = 0;
-    if (cnt)
+    if (cnt) {
+      // (bitwise, so that the LDS reads of several j are in flight together)
+#pragma unroll 8
       for (int j = 0; j < E; ++j)
-        start += s_ok[j] && (s_rows[j] > rows || (s_rows[j] == rows && j < e));
+        start += s_ok[j] & ((int)(s_rows[j] > rows) | ((int)(s_rows[j] == rows) & (int)(j < e)));
+    }
   }
   if (mode == 0) {
     for (int i = 0; i < cnt; ++i) {
