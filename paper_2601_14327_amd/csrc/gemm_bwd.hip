@@ -456,7 +456,9 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
         issue_half(3);
 #pragma unroll
         for (int i = 0; i < NH; ++i) g[i] = p.gate[s1[i]];
-        wait_vmcnt<3 * NH>();
+        // A of step 1 too: the loop's wait for it counts the four gate loads behind
+        // it, which the compiler may issue before it here (B of step 1 follows it)
+        wait_vmcnt<NH>();
       } else {
 #pragma unroll
         for (int i = 0; i < NH; ++i) {   // data gradient 1: the chunk rows' gates, once
@@ -521,7 +523,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_bwd_kernel(GemmParams p) 
       });
       // dY on load: this thread's copies of the A half of step kt+1 have landed
       // once only what was issued after them may be in flight: B of kt+1 and A of
-      // kt+2, and for dW_d the gates of kt+1 and the row ids of kt+3.  It scales
+      // kt+2, and for dW_d the gates of kt+1 and the row ids of kt+3 (in the first
+      // step they had landed before the loop).  It scales
       // its chunks in place, read beside sub-step 1, scaled and written beside
       // sub-step 2; the boundary's lgkmcnt(0) and barrier publish them.
       u32x4_t dy[NH];
