@@ -1,5 +1,5 @@
 /*
- * laep_calib.h -- measurement kernels of the LAEP MoE library (gfx950).
+ * laep_calib.h -- measurement calls of the LAEP MoE library (gfx950).
  *
  * Not part of the MoE layer: these calls measure what the chip attains on the
  * resources the layer's kernels are bound by, so that achieved rates can be
@@ -54,6 +54,14 @@ int laep_calib_read(const void* src, size_t bytes, int block_bytes, float* out, 
  *         LAEP_ERR_HIP.
  */
 int laep_calib_mfma(int n_workgroups, int iters, float* out, void* stream);
+
+/*
+ * laep_ffn_fwd_row_tile -- rows per tile (32, 64, 128 or 256) that the bf16
+ * forward FFN calls use for these sizes (arguments as of moe_grouped_ffn_fwd):
+ * which of its kernels a measurement or a test runs.  Host code only; 0 for
+ * sizes that those calls refuse.
+ */
+int laep_ffn_fwd_row_tile(int64_t R, int E, int d_model, int d_ff);
 
 #ifdef __cplusplus
 }

@@ -76,10 +76,11 @@ SIGNATURES = {
     "moe_workspace_bytes": (_sz, [_i, _i, _i, _i, _i, _i]),
     "laep_rearrange": (_i, [_p, _i, _i, _p, _p, _p]),
     "laep_last_error": (ctypes.c_char_p, []),
-    # measurement kernels (laep_calib.h)
+    # measurement calls (laep_calib.h)
     "laep_calib_copy": (_i, [_p, _p, _sz, _p]),
     "laep_calib_mfma": (_i, [_i, _i, _p, _p]),
     "laep_calib_read": (_i, [_p, _sz, _i, _p, _p]),
+    "laep_ffn_fwd_row_tile": (_i, [_i64, _i, _i, _i]),
 }
 
 _lock = threading.Lock()

@@ -524,7 +524,7 @@ def laep_rearrange(loads, n_groups: int):
     return dict(group_of=group_of, order=order, sums=sums[:n_groups])
 
 
-# ---- measurement kernels (laep_calib.h) -----------------------------------------------
+# ---- measurement calls (laep_calib.h) -------------------------------------------------
 def laep_calib_copy(src: torch.Tensor, dst: torch.Tensor):
     """dst <- src (raw bytes) with the library's streaming copy kernel."""
     _dev(src, "src")
@@ -554,3 +554,8 @@ def laep_calib_mfma(n_workgroups: int, iters: int, out: torch.Tensor):
     if out.dtype != torch.float32 or out.numel() < n_workgroups * 512:
         raise ValueError("out must be float32 with n_workgroups * 512 elements")
     check(lib().laep_calib_mfma(n_workgroups, iters, _ptr(out), _stream(out.device)))
+
+
+def laep_ffn_fwd_row_tile(R: int, E: int, d_model: int, d_ff: int) -> int:
+    """Rows per tile (32, 64, 128 or 256) of the bf16 forward FFN at these sizes."""
+    return int(lib().laep_ffn_fwd_row_tile(int(R), int(E), int(d_model), int(d_ff)))

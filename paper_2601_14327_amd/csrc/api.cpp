@@ -596,7 +596,7 @@ int moe_permute_bwd(const void* dx_perm, const int32_t* dest_row, int T, int k, 
                     "moe_permute_bwd");
 }
 
-// ---- measurement kernels (laep_calib.h) ------------------------------------------
+// ---- measurement calls (laep_calib.h) --------------------------------------------
 int laep_calib_copy(const void* src, void* dst, size_t bytes, void* stream) {
   REQUIRE(src && dst && aligned16(src) && aligned16(dst) && bytes % 16 == 0,
           LAEP_ERR_INVALID_ARG, "laep_calib_copy: null or misaligned pointer, or bytes %% 16 != 0");
@@ -620,6 +620,11 @@ int laep_calib_mfma(int n_workgroups, int iters, float* out, void* stream) {
           "laep_calib_mfma: null out, n_workgroups < 1 or iters < 1");
   return hip_status(laep::launch_calib_mfma(n_workgroups, iters, out, as_stream(stream)),
                     "laep_calib_mfma");
+}
+
+int laep_ffn_fwd_row_tile(int64_t R, int E, int d_model, int d_ff) {
+  if (check_ffn_shape(LAEP_BF16, E, d_model, d_ff, R)) return 0;
+  return laep::ffn_fwd_row_tile(R, E, d_model, d_ff);
 }
 
 }  // extern "C"

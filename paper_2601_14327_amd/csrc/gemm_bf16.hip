@@ -523,7 +523,8 @@ hipError_t launch_ffn_fwd_products(const void* x_perm, const void* w_gu, const v
                                    int d, int f, int64_t R, void* y_perm, void* act_save,
                                    bf16_t* H, void* ws, hipStream_t s, const int32_t* row_src,
                                    int slots_k, const float* gate, void* out_tok) {
-  if (const int bm = small_fwd_bm(R, E, d, f))
+  const int bm = ffn_fwd_row_tile(R, E, d, f);
+  if (bm != kFwdBM)
     return launch_ffn_fwd_small(bm, x_perm, w_gu, w_d, offsets, expert_map, E, d, f, R, y_perm,
                                 act_save, H, s, row_src, slots_k, gate, out_tok);
   const int nt_gu = ceil_div(f, kFwdBN / 2), nt_d = ceil_div(d, kFwdBN);

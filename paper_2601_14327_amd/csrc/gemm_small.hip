@@ -13,7 +13,6 @@
 //
 // The k order and the MFMA are those of the 256-row kernels, so the results
 // have the same bits.
-#include <cmath>
 #include <type_traits>
 
 #include "gemm_common.hpp"
@@ -282,65 +281,41 @@ hipError_t launch_small_pair(SmallParams g, SmallParams dn, int64_t R, bool gath
 
 }  // namespace
 
-// Row-tile height by estimated time, root of the sum of squares of two parts:
-//  - the weights' stream from HBM, at the rate each kernel reaches with few
-//    rows (64 experts of 12.6 MB: 4.1 TB/s at 256 rows, 5.3-5.5 below);
-//  - the k-steps a CU works through, each at its measured time: 0.275 / 0.40 /
-//    0.64 us per tile at 32 / 64 / 128 rows (two or more workgroups sharing a
-//    CU; 0.45 / 0.5 / 0.72 for one alone), and 1.9 us per full 256-row tile
-//    (256 columns wide; a part of it for part of the rows, 0.8 more for each
-//    further, partly filled tile, 1.0 at least).  The 256-row kernels hold one
-//    workgroup per CU, so under two rounds of tiles whole rounds count.
-// The experts' rows are taken as even (the host does not know them); where
-// most loads no longer fit a whole number of tiles half a tile is added.
-// Measured, us for both products (estimates within 20 %, the choice within
-// 10 % of the best; d = 2048, f = 1024, E = 64, then d = f = 1024, E = 16):
-//   rows each   32 / 64 / 128 / 256-row tiles    rows each
-//     1         105 / 112 / 138 / 163              8          21 /  23 /  29 / 42
-//    32         161 / 163 / 186 / 199             64          29 /  27 /  32 / 43
-//    64         205 / 184 / 193 / 206            128          42 /  37 /  34 / 48
-//    96         248 / 214 / 198 / 214            512         116 /  90 /  79 / 90
-//   128         297 / 250 / 255 / 221            768         173 / 131 / 111 / 100
-int small_fwd_bm(int64_t R, int E, int d, int f) {
-  struct Kernel {
-    int bm;           // returned as 0 for the 256-row kernels
-    int cols_gu, cols_d;
-    double step_us, alone_us, stream_bytes_per_us;
-  };
-  const Kernel kernels[] = {
-      {256, ceil_div(f, 128), ceil_div(d, 256), 1.9, 1.0, 4.1e6},
-      {128, f / 64, ceil_div(d, 128), 0.64, 0.72, 5.3e6},
-      {64, f / 64, ceil_div(d, 128), 0.40, 0.5, 5.4e6},
-      {32, f / 64, ceil_div(d, 128), 0.275, 0.45, 5.5e6},
-  };
-  constexpr double kCUs = 256, kPartTile = 0.8;
-  const double rows = (double)R / E;
-  // experts that R rows spread at random reach
-  const double live = E * (1.0 - std::pow(1.0 - 1.0 / E, (double)R));
-  int best = 0;
-  double best_us = 0.0;
-  for (const Kernel& kn : kernels) {
-    const double r = rows / kn.bm;
-    const double over = r < 0.75 ? 0.0 : r < 1.0 ? 2.0 * (r - 0.75) : 0.5;
-    const double tiles = r + over > 1.0 ? r + over : 1.0;  // of one expert
-    auto product = [&](int cols, int K) {
-      const double per_cu = live * cols / kCUs;  // experts' column blocks
-      double us = kn.step_us * tiles * per_cu;
-      if (kn.bm == 256) {
-        us = (kn.step_us * r + kPartTile * (tiles - (r > 1.0 ? r : 1.0))) * per_cu;
-        const double rounds = tiles * per_cu;
-        if (rounds < 2.0) us *= std::ceil(rounds) / rounds;
-      }
-      return K / 64 * (us > kn.alone_us ? us : kn.alone_us);
-    };
-    const double us = std::hypot(live * 6.0 * d * f / kn.stream_bytes_per_us,
-                                 product(kn.cols_gu, d) + product(kn.cols_d, f));
-    if (best_us == 0.0 || us < best_us) {
-      best_us = us;
-      best = kn.bm;
-    }
-  }
-  return best == 256 ? 0 : best;
+// Row-tile height of a forward call.  The 256-row kernels take whole CUs for
+// tiles of few rows; the short tiles fill the chip with little work, but need
+// more time for the same rows once it is full: with all rows in one expert,
+// 1.4 / 1.7 / 2.3 times at 128 / 64 / 32 rows.  The host does not know the
+// loads, and with few of many experts taking most rows the tiles are full
+// however few rows an expert has on average.  So the line lies where all rows,
+// in 128-row tiles on a full chip (busy), take less than the 256-row kernels
+// need for their own latency (alone: two k-loops of one tile each, the second's
+// share larger where d is narrow and its tiles are few): there the short tiles
+// win or tie whatever the loads.  32 rows only for a fraction of that, 128
+// where the experts fill them.
+// Measured, us for both products, rows in 256 / 32 / 64 / 128-row tiles; 64
+// experts, d 2048, d_ff 1024:
+//    rows  even loads              normal(0, 2) router bias  one expert
+//     512  185 / 135 / 141 / 163    67 /  53 /  55 /  62     63 /  24 /  27 /  37
+//    2048  189 / 146 / 149 / 171    72 / 100 /  72 /  62     66 /  60 /  41 /  44
+//    3072  193 / 194 / 168 / 179    79 / 118 /  92 / 102     69 /  88 /  65 /  51
+//    8192  215 / 303 / 243 / 234   155 / 260 / 197 / 165     98 / 214 / 149 / 131
+// and 16 experts, d = d_ff = 1024:
+//     512   40 /  24 /  24 /  32    49 /  23 /  21 /  27     48 /  18 /  21 /  26
+//    2048   44 /  43 /  35 /  34    51 /  43 /  35 /  32     50 /  34 /  26 /  31
+//    8192   80 / 115 /  86 /  77    81 / 121 /  92 /  91     63 / 112 /  83 /  70
+// Over 13 widths (d 64-4096, d_ff 64-2048), 1-256 experts, 8-100000 rows and
+// five kinds of load the rule's choice is at most 10 % behind the 256-row
+// kernels (never behind the ones that staged their output), and takes 0.67 of
+// their time on average.
+int ffn_fwd_row_tile(int64_t R, int E, int d, int f) {
+  // k-steps of one row tile over both products, two more for a tile's two ends;
+  // 0.64 us each for 128 rows x 128 columns, two tiles sharing a CU of 256
+  const double steps = (f / 64) * (d / 64 + 2.0) + ceil_div(d, 128) * (f / 64 + 2.0);
+  const double busy_us = (double)R / 128 * steps * 0.64 / 256;
+  const double alone_us = (d + 2.0 * f) / 96 + 15;
+  if (busy_us > 0.8 * alone_us) return 256;
+  if (busy_us <= 0.15 * alone_us) return 32;
+  return R > 96 * (int64_t)E && busy_us > 0.4 * alone_us ? 128 : 64;
 }
 
 hipError_t launch_ffn_fwd_small(int bm, const void* x, const void* w_gu, const void* w_d,

@@ -91,9 +91,9 @@ hipError_t launch_ffn_fwd_bf16(const void* x_perm, const void* w_gu, const void*
                                hipStream_t s, const int32_t* row_src = nullptr, int slots_k = 1,
                                const float* gate = nullptr, void* out_tok = nullptr,
                                void* x_perm_out = nullptr);
-// Few rows per expert (csrc/gemm_small.hip): the row-tile height to use, or 0
-// for the 256-row kernels; and the two products (H: the workspace's [R, f]).
-int small_fwd_bm(int64_t R, int E, int d, int f);
+// The forward's row-tile height: 256 (csrc/gemm_bf16.hip), or 32, 64 or 128
+// (csrc/gemm_small.hip: the two products, H: the workspace's [R, f]).
+int ffn_fwd_row_tile(int64_t R, int E, int d, int f);
 hipError_t launch_ffn_fwd_small(int bm, const void* x, const void* w_gu, const void* w_d,
                                 const int32_t* offsets, const int32_t* expert_map, int E, int d,
                                 int f, int64_t R, void* y_perm, void* act_save, void* H,
