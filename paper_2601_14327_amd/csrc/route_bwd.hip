@@ -562,8 +562,15 @@ size_t route_bwd_ws_bytes(int T, int k, int E, int d) {
   const int m = seg_max(T, k, E);
   const size_t seg = table_bytes(m) + align_up((size_t)m * d * sizeof(float), 256) +
                      align_up((size_t)m * sizeof(float), 256);
-  const size_t n = dense_split(T, E, d).n;
-  const size_t dense = align_up(n * E * d * sizeof(float), 256) + align_up(n * E * sizeof(float), 256);
+  // not the dense product's own splits, whose number falls where a split gains a
+  // step or the output a tile, but bounds that grow with every size, so that a
+  // workspace for the largest call serves the smaller ones: at most 512 and T / 64
+  // splits (rounded up), and less than 512 tiles of 64 x 128 beyond one output
+  const size_t n = (size_t)(T + 63) / 64 < 512 ? (size_t)(T + 63) / 64 : 512;
+  auto least = [](size_t a, size_t b) { return a < b ? a : b; };
+  const size_t dense =
+      align_up(least(n * E * d, (size_t)512 * kDenseBM * kDenseBN + (size_t)E * d) * sizeof(float), 256) +
+      align_up(least(n * E, (size_t)512 * kDenseBM + E) * sizeof(float), 256);
   return align_up((size_t)T * k * sizeof(float), 256) + align_up((size_t)T * E * sizeof(float), 256) +
          (seg > dense ? seg : dense);
 }
