@@ -284,8 +284,11 @@ int laep_repack_experts(const int32_t* expert_map, int E, int n_out, int dtype,
  *   weight gradients as soon as dgate exists and dx once the expert path's dx
  *   does (two calls, two workspaces).
  *   renorm = 1 needs offsets [E + 1] and row_src [T * k] from
- *   moe_expert_counts on the same topk_idx (dw_router is summed over each
- *   expert's routed rows in that order); logits and alive may be NULL.
+ *   moe_expert_counts on the same topk_idx; logits and alive may be NULL.
+ *   dw_router is summed over each expert's routed rows in that order, or, with
+ *   few experts or many slots, over all tokens in order (dl is 0 for the others);
+ *   an infinite or NaN element of x reaches only the experts of its token's slots
+ *   either way.
  *   renorm = 0 needs logits [T, E] (moe_route's float32 logits output) and
  *   the alive mask moe_route used (NULL = all alive).
  *   Workspace: moe_workspace_bytes(LAEP_CALL_ROUTE_BWD, T, k, E, d_model, 0).

@@ -264,15 +264,15 @@ template <> struct Wide8<float> {
 
 // Mrows: rows of the output (tokens for kDx, experts for kDw); K: the
 // reduction length; k_per: its length per split (a multiple of 32).
-// SPARSE (kDw): dl is zero outside each token's selected experts, and an expert's
-// row may see only its own tokens: 0 * x must stay 0 for an infinite or NaN x.
-// Such elements are left out of the matrix product and added afterwards to the
-// experts whose dl is not zero (they make those sums infinite or NaN in any order).
+// SPARSE (kDw): dl is zero outside each token's selected experts (idx [T, k]), and
+// an expert's row may see only its own tokens: 0 * x must stay 0 for an infinite
+// or NaN x.  Such elements are left out of the matrix product and added
+// afterwards, in token order, to the experts that the token selected.
 template <typename T, int MODE, bool SPARSE = false>
 __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
     const float* __restrict__ dl, const T* __restrict__ B, const uint8_t* __restrict__ alive,
     int Mrows, int K, int k_per, int E, int d, int accumulate, T* __restrict__ dx, float* __restrict__ part,
-    float* __restrict__ part_b) {
+    float* __restrict__ part_b, const int32_t* __restrict__ idx, int k) {
   constexpr int BM = kDenseBM, BN = kDenseBN, KC = kDenseKC;
   constexpr int LDA = BM + 33, LDB = BN + 4;  // LDA odd: transposed writes spread over the banks
   __shared__ float sA[KC * LDA];
@@ -351,12 +351,31 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
   }
 
   const int row = m0 + wm * 32 + lr;
+  auto column = [&](int j, int q) { return n0 + wn * 64 + j * 32 + q * 8 + h * 4; };
+  if constexpr (SPARSE) {
+    // the elements left out, by the lanes that own their sums
+    if (__syncthreads_or(nonfinite ? 1 : 0) && row < Mrows)
+      for (int kk = k0; kk < k1; ++kk) {
+        bool selected = false;
+        for (int s = 0; s < k; ++s) selected |= idx[(size_t)kk * k + s] == row;
+        if (!selected) continue;
+        const float w = dl[(size_t)kk * E + row];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int c = column(j, r >> 2) + (r & 3);
+            const float v = c < d ? widen(B[(size_t)kk * d + c]) : 0.0f;
+            if (!(fabsf(v) < INFINITY)) acc[j][r] += w * v;
+          }
+      }
+  }
   if (row < Mrows) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int c = n0 + wn * 64 + j * 32 + q * 8 + h * 4;
+        const int c = column(j, q);
         if (c >= d) continue;
         f32x4_t v = {acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
         if constexpr (MODE == kDw) {
@@ -376,23 +395,6 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
       }
   }
   if (sums_bias && m0 + tid < Mrows) part_b[(size_t)blockIdx.z * Mrows + m0 + tid] = bias;
-  if constexpr (SPARSE) {
-    // the elements left out, after the tile's stores (same workgroup, so the
-    // barrier orders them)
-    if (__syncthreads_or(nonfinite ? 1 : 0)) {
-      const int m1 = min(Mrows, m0 + BM);
-      for (int q = tid; q < (k1 - k0) * BN; q += 256) {
-        const int kk = k0 + q / BN, c = n0 + q % BN;
-        if (c >= d) continue;
-        const float v = widen(B[(size_t)kk * d + c]);
-        if (fabsf(v) < INFINITY) continue;
-        for (int m = m0; m < m1; ++m) {
-          const float w = dl[(size_t)kk * E + m];
-          if (w != 0.0f) atomicAdd(part + ((size_t)blockIdx.z * Mrows + m) * d + c, w * v);
-        }
-      }
-    }
-  }
 }
 
 // dW_r = sum of the splits' partial tiles in split order, db likewise.  One
@@ -580,7 +582,7 @@ namespace {
 // dW_r (and db) from the dense dl [T, E]
 template <typename T, bool SPARSE>
 void launch_dense_dw(const float* dl, const T* x, int T_, int E, int d, char* base,
-                     float* dw_router, float* dbias, hipStream_t s) {
+                     float* dw_router, float* dbias, const int32_t* idx, int k, hipStream_t s) {
   const DenseSplit sp = dense_split(T_, E, d);
   float* part = reinterpret_cast<float*>(base);
   float* part_b = reinterpret_cast<float*>(base + align_up((size_t)sp.n * E * d * sizeof(float), 256));
@@ -588,7 +590,7 @@ void launch_dense_dw(const float* dl, const T* x, int T_, int E, int d, char* ba
                      dim3((unsigned)((E + kDenseBM - 1) / kDenseBM),
                           (unsigned)((d + kDenseBN - 1) / kDenseBN), (unsigned)sp.n),
                      dim3(256), 0, s, dl, x, nullptr, E, T_, sp.per, E, d, 0,
-                     static_cast<T*>(nullptr), part, dbias ? part_b : nullptr);
+                     static_cast<T*>(nullptr), part, dbias ? part_b : nullptr, idx, k);
   const size_t n = (size_t)E * d;  // >= E
   hipLaunchKernelGGL(route_bwd_dense_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256),
                      0, s, part, part_b, sp.n, E, d, dw_router, dbias);
@@ -613,8 +615,8 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
                          dim3((unsigned)((T_ + kDenseBM - 1) / kDenseBM),
                               (unsigned)((d + kDenseBN - 1) / kDenseBN)),
                          dim3(256), 0, s, dl_dense, w_router, alive, T_, E, E, E, d, accumulate_dx,
-                         dx, nullptr, nullptr);
-    if (dw_router) launch_dense_dw<T, false>(dl_dense, x, T_, E, d, base, dw_router, dbias, s);
+                         dx, nullptr, nullptr, nullptr, 0);
+    if (dw_router) launch_dense_dw<T, false>(dl_dense, x, T_, E, d, base, dw_router, dbias, idx, k, s);
     return hipGetLastError();
   }
   const bool dense = dw_router && renorm_dw_dense(k, E);
@@ -624,7 +626,7 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
     hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,
                        w_router, idx, dl, T_, k, d, accumulate_dx, dx);
   if (dense) {
-    launch_dense_dw<T, true>(dl_dense, x, T_, E, d, base, dw_router, dbias, s);
+    launch_dense_dw<T, true>(dl_dense, x, T_, E, d, base, dw_router, dbias, idx, k, s);
   } else if (dw_router) {
     // segment table of the routed rows (pass 1 + 2)
     const int m = seg_max(T_, k, E);

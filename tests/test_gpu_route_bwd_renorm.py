@@ -54,7 +54,8 @@ def test_weights(T, E, k, d, dtype):
 
 
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
-@pytest.mark.parametrize("E,k", [(64, 4), (130, 4)])
+@pytest.mark.parametrize("E,k", [(64, 4), (130, 4),
+                                 (64, 1), (130, 1)])   # one slot: dl is 0, and 0 * inf NaN
 def test_infinite_token(E, k, bad):
     T, d = 200, 136
     case(f"router renorm weights, token with {bad} E={E}")
@@ -70,3 +71,34 @@ def test_infinite_token(E, k, bad):
     ok = torch.ones_like(ref, dtype=torch.bool)
     ok[hit, c] = False
     assert torch.equal(got[ok], ref[ok])
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("E,k", [(64, 4), (130, 4)])
+def test_several_infinite_tokens(E, k, dtype):
+    """Two and three tokens of one expert in one split, of both signs and NaN: the
+    expert's sums are what they are in token order, every bit the same each time."""
+    T, d = 640, 264
+    case(f"router renorm weights, several non-finite tokens E={E} {dtype}")
+    x, wr, idx, gate, off, src, dg = _inputs(T, E, k, d, dtype, E + 1)
+    e = int(idx[300, 0])
+    toks = (idx == e).any(1).nonzero().flatten()[:3].tolist()
+    assert len(toks) == 3
+    cols = {5: [float("inf"), float("inf")], 130: [float("inf"), float("-inf")],
+            261: [float("-inf"), float("nan"), float("inf")]}
+    xz, xb = x.clone(), x.clone()
+    hit = torch.zeros((E, d), dtype=torch.bool, device="cuda")
+    for c, vals in cols.items():
+        for t, v in zip(toks, vals):
+            xz[t, c], xb[t, c] = 0.0, v
+            hit[idx[t].long(), c] = True
+    ref = _dw(xz, wr, idx, gate, off, src, dg)[0]
+    got, _, dl = _dw(xb, wr, idx, gate, off, src, dg)
+    for _ in range(4):
+        again = _dw(xb, wr, idx, gate, off, src, dg)[0]
+        assert torch.equal(got.view(torch.int32), again.view(torch.int32))
+    assert torch.equal(got[~hit], ref[~hit])
+    for m, c in hit.nonzero().tolist():
+        rows = (idx == m).any(1)
+        want = (dl[rows, m] * xb[rows, c].float()).sum().item()   # inf, -inf or NaN in any order
+        assert str(got[m, c].item()) == str(want)
