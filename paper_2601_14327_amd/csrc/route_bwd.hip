@@ -11,6 +11,8 @@
 // dense over the alive experts; dx then sums over all E experts and dW_r over all
 // T tokens.
 // Every sum runs in a fixed order: results are deterministic.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 #include "tiles.hpp"
@@ -219,16 +221,12 @@ template <typename T> struct Wide8;  // 8 consecutive elements -> fp32
 template <> struct Wide8<bf16_t> {
   u32x4_t r;
   __device__ __forceinline__ void zero() { r = u32x4_t{0u, 0u, 0u, 0u}; }
-  // infinities and NaNs to zero; true if there were any
-  __device__ __forceinline__ bool drop_nonfinite() {
-    bool bad = false;
+  __device__ __forceinline__ void drop_nonfinite() {  // infinities and NaNs to zero
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const bool lo = (r[i] & 0x7f80u) == 0x7f80u, hi = (r[i] & 0x7f800000u) == 0x7f800000u;
-      bad |= lo | hi;
       r[i] &= (lo ? 0xffff0000u : ~0u) & (hi ? 0xffffu : ~0u);
     }
-    return bad;
   }
   __device__ __forceinline__ void load(const bf16_t* p) {
     r = *reinterpret_cast<const u32x4_t*>(p);
@@ -241,16 +239,12 @@ template <> struct Wide8<bf16_t> {
 template <> struct Wide8<float> {
   f32x4_t a, b;
   __device__ __forceinline__ void zero() { a = b = f32x4_t{0.f, 0.f, 0.f, 0.f}; }
-  __device__ __forceinline__ bool drop_nonfinite() {
-    bool bad = false;
+  __device__ __forceinline__ void drop_nonfinite() {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const bool ba = !(fabsf(a[i]) < INFINITY), bb = !(fabsf(b[i]) < INFINITY);
-      bad |= ba | bb;
-      a[i] = ba ? 0.0f : a[i];
-      b[i] = bb ? 0.0f : b[i];
+      a[i] = fabsf(a[i]) < INFINITY ? a[i] : 0.0f;
+      b[i] = fabsf(b[i]) < INFINITY ? b[i] : 0.0f;
     }
-    return bad;
   }
   __device__ __forceinline__ void load(const float* p) {
     a = *reinterpret_cast<const f32x4_t*>(p);
@@ -264,10 +258,15 @@ template <> struct Wide8<float> {
 
 // Mrows: rows of the output (tokens for kDx, experts for kDw); K: the
 // reduction length; k_per: its length per split (a multiple of 32).
-// SPARSE (kDw): dl is zero outside each token's selected experts (idx [T, k]), and
-// an expert's row may see only its own tokens: 0 * x must stay 0 for an infinite
-// or NaN x.  Such elements are left out of the matrix product and added
-// afterwards, in token order, to the experts that the token selected.
+// An infinite or NaN element of B must not reach the outputs whose dl is 0.  A tile
+// whose sums are not all finite is formed again without such elements (the other
+// sums keep their bits), and they are added afterwards, in the order of k, by the
+// lanes that own the sums.
+//   kDx: to the tokens whose dl is not 0 (an expert of probability 0 carries none,
+//        whatever its row of W_r holds);
+//   kDw, SPARSE (dl is 0 outside each token's selected experts, idx [T, k]): to the
+//        experts that the token selected.
+// kDw of full-softmax gates needs neither: every alive expert sees every token.
 template <typename T, int MODE, bool SPARSE = false>
 __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
     const float* __restrict__ dl, const T* __restrict__ B, const uint8_t* __restrict__ alive,
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
   const int k0 = blockIdx.z * k_per, k1 = min(K, k0 + k_per);
 
   static_assert(!SPARSE || MODE == kDw, "dx reads every alive expert's row");
-  bool nonfinite = false;
+  constexpr bool APART = SPARSE || MODE == kDx;
   float ra[BM * KC / 256];
   Wide8<T> rb[KC * BN / 8 / 256];
   auto load = [&](int kb) {
@@ -307,7 +306,7 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
       else rb[i].zero();
     }
   };
-  auto store = [&]() {
+  auto store = [&](auto finite_only) {
 #pragma unroll
     for (int i = 0; i < BM * KC / 256; ++i) {
       const int q = i * 256 + tid;
@@ -317,49 +316,58 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
 #pragma unroll
     for (int i = 0; i < KC * BN / 8 / 256; ++i) {
       const int q = i * 256 + tid;
-      if constexpr (SPARSE) nonfinite |= rb[i].drop_nonfinite();
+      if constexpr (decltype(finite_only)::value) rb[i].drop_nonfinite();
       rb[i].put(sB + (q / (BN / 8)) * LDB + (q % (BN / 8)) * 8);
     }
   };
   f32x16_t acc[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
   const bool sums_bias = MODE == kDw && part_b != nullptr && blockIdx.y == 0 && tid < BM;
-  float bias = 0.0f;
+  float bias;
 
   const int lr = lane & 31, h = lane >> 5;
-  if (k0 < k1) load(k0);
-  for (int kb = k0; kb < k1; kb += KC) {
-    store();
-    __syncthreads();
-    if (kb + KC < k1) load(kb + KC);
+  auto product = [&](auto finite_only) {
 #pragma unroll
-    for (int s = 0; s < KC / 2; ++s) {
-      const float a = sA[(2 * s + h) * LDA + wm * 32 + lr];
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const float b = sB[(2 * s + h) * LDB + wn * 64 + j * 32 + lr];
-        acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, acc[j], 0, 0, 0);
+      for (int r = 0; r < 16; ++r) acc[j][r] = 0.0f;
+    bias = 0.0f;
+    if (k0 < k1) load(k0);
+    for (int kb = k0; kb < k1; kb += KC) {
+      store(finite_only);
+      __syncthreads();
+      if (kb + KC < k1) load(kb + KC);
+#pragma unroll
+      for (int s = 0; s < KC / 2; ++s) {
+        const float a = sA[(2 * s + h) * LDA + wm * 32 + lr];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const float b = sB[(2 * s + h) * LDB + wn * 64 + j * 32 + lr];
+          acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, acc[j], 0, 0, 0);
+        }
       }
-    }
-    if (sums_bias)
+      if (sums_bias)
 #pragma unroll
-      for (int kk = 0; kk < KC; ++kk) bias += sA[kk * LDA + tid];
-    __syncthreads();
-  }
+        for (int kk = 0; kk < KC; ++kk) bias += sA[kk * LDA + tid];
+      __syncthreads();
+    }
+  };
+  product(std::false_type{});
 
   const int row = m0 + wm * 32 + lr;
   auto column = [&](int j, int q) { return n0 + wn * 64 + j * 32 + q * 8 + h * 4; };
-  if constexpr (SPARSE) {
-    // the elements left out, by the lanes that own their sums
-    if (__syncthreads_or(nonfinite ? 1 : 0) && row < Mrows)
-      for (int kk = k0; kk < k1; ++kk) {
-        bool selected = false;
-        for (int s = 0; s < k; ++s) selected |= idx[(size_t)kk * k + s] == row;
-        if (!selected) continue;
-        const float w = dl[(size_t)kk * E + row];
+  if constexpr (APART) {
+    float any = 0.0f;  // stays 0 while every sum is finite
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) any = fmaf(acc[j][r], 0.0f, any);
+    if (__syncthreads_or(any != 0.0f ? 1 : 0)) {
+      product(std::true_type{});
+      for (int kk = k0; kk < (row < Mrows ? k1 : k0); ++kk) {
+        const float w = MODE == kDx ? dl[(size_t)row * E + kk] : dl[(size_t)kk * E + row];
+        bool seen = MODE == kDx && w != 0.0f;  // (0 for a pruned expert)
+        for (int s = 0; SPARSE && s < k; ++s) seen |= idx[(size_t)kk * k + s] == row;
+        if (!seen) continue;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -369,6 +377,7 @@ __global__ __launch_bounds__(256) void route_bwd_dense_kernel(
             if (!(fabsf(v) < INFINITY)) acc[j][r] += w * v;
           }
       }
+    }
   }
   if (row < Mrows) {
 #pragma unroll

@@ -49,3 +49,35 @@ def test_dense_route_bwd(T, d, E, k, dtype, dead):
         assert rownorm_err(host(dw), rw) <= TOL_F32
         assert rownorm_err(host(db), rb) <= TOL_F32
         assert rownorm_err(host(dx), rx) <= (TOL_BF16 if dtype == "bf16" else TOL_F32)
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+@pytest.mark.parametrize("T,d,E,k,dtype", [(200, 136, 70, 4, "bf16"), (65, 264, 33, 2, "f32")])
+def test_probability_zero_keeps_nonfinite_rows_out_of_dx(T, d, E, k, dtype, bad):
+    """An expert whose logit is -inf for a token has dl = 0 there: its row of W_r,
+    whatever it holds, does not reach that token's dx; elsewhere it does."""
+    td = TD[dtype]
+    case(f"dense route bwd, non-finite W_r T={T} d={d} E={E} k={k} {dtype} {bad}")
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    x = torch.randn((T, d), generator=g, device="cuda").to(td)
+    wr = (0.05 * torch.randn((E, d), generator=g, device="cuda")).to(td)
+    logits = torch.randn((T, E), generator=g, device="cuda")
+    nowhere, some, c = E // 3, E - 1, d - 7
+    logits[:, nowhere] = -float("inf")
+    logits[: T // 2, some] = -float("inf")
+    p = torch.softmax(logits, 1)
+    gate, idx = torch.topk(p, k, dim=1)
+    dg = torch.randn((T, k), generator=g, device="cuda")
+    base = torch.randn((T, d), generator=g, device="cuda").to(td)
+    wz, wb = wr.clone(), wr.clone()
+    wz[nowhere], wb[nowhere] = 0.0, bad
+    wz[some, c], wb[some, c] = 0.0, bad
+    for acc in (False, True):
+        ref, got = (laep.moe_route_bwd(dg, idx.int().contiguous(), gate.contiguous(), x, w,
+                                       renorm=False, logits=logits, dx=base.clone(),
+                                       accumulate_dx=acc, weights=False)[0] for w in (wz, wb))
+        torch.cuda.synchronize()
+        hit = torch.zeros((T, d), dtype=torch.bool, device="cuda")
+        hit[T // 2:, c] = True
+        assert not torch.isfinite(got[hit]).any()
+        assert torch.isfinite(ref).all() and torch.equal(got[~hit], ref[~hit])
