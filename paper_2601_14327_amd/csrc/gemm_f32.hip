@@ -38,7 +38,9 @@ __global__ __launch_bounds__(kF32Threads) void gemm_f32_kernel(
   constexpr int LD = kT + 4;       // floats per staged row
   __shared__ __attribute__((aligned(16))) float s_part[kF32Waves * NB * kT * LD];
   FoundTile te;
-  if (!find_tile(offsets, expert_map, E, kT, n_tiles_n, reinterpret_cast<char*>(s_part), te)) return;
+  if (!find_tile(blockIdx.y * gridDim.x + blockIdx.x, offsets, expert_map, E, kT, n_tiles_n,
+                 reinterpret_cast<char*>(s_part), te))
+    return;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int lr = lane & 31, h = lane >> 5;
   const int n0 = te.nt * kT;
@@ -129,9 +131,13 @@ hipError_t launch_ffn_fwd_f32(const void* x_perm, const void* w_gu, const void* 
   if (R <= 0) return hipSuccess;
   float* H = static_cast<float*>(ws);
   // sum of ceil(rows / kT) over the experts with rows, to a multiple of 8 (the
-  // tile search takes one range per XCD)
+  // tile search takes one range per XCD); in two dimensions, since one holds
+  // less than 2^32 threads
   const int64_t rows = R / kT + (R < E ? R : E);
-  auto grid = [&](int n_tiles_n) { return dim3((unsigned)((rows * n_tiles_n + 7) / 8 * 8)); };
+  auto grid = [&](int n_tiles_n) {
+    const int64_t blocks = (rows * n_tiles_n + 7) / 8 * 8, x = blocks < 1 << 20 ? blocks : 1 << 20;
+    return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
+  };
   const int nt_gu = f / kT, nt_d = d / kT;
   hipLaunchKernelGGL((gemm_f32_kernel<true>), grid(nt_gu), dim3(kF32Threads), 0, s,
                      static_cast<const float*>(x_perm), d, static_cast<const float*>(w_gu), d,

@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kSmallThreads) void gemm_small_kernel(SmallParams p
   const int tid = threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
   FoundTile te;
-  if (!find_tile(p.offsets, p.expert_map, p.E, BM, p.n_tiles_n, smem, te)) return;
+  if (!find_tile(blockIdx.x, p.offsets, p.expert_map, p.E, BM, p.n_tiles_n, smem, te)) return;
   const int nt = te.nt;
 
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);

@@ -208,13 +208,13 @@ struct FoundTile : TileEntry {
   int expert_rows;
 };
 
-// The tile of this workgroup, found from the expert offsets (no list): tiles
+// The tile of workgroup `block`, found from the expert offsets (no list): tiles
 // of BM rows x n_tiles column blocks, experts in order, within an expert the
 // row tiles of a column block innermost (they share its weights); te also
 // says how many rows the expert has in all.  Each XCD
 // takes a contiguous range (block i runs on XCD i % 8).  256 threads, one per
 // expert; scratch: LDS, free again on return.  False: no tile.
-__device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets,
+__device__ __forceinline__ bool find_tile(unsigned block, const int32_t* __restrict__ offsets,
                                           const int32_t* __restrict__ expert_map, int E, int BM,
                                           int n_tiles, char* scratch, FoundTile& te) {
   int* const s_wave = reinterpret_cast<int*>(scratch);
@@ -244,8 +244,8 @@ __device__ __forceinline__ bool find_tile(const int32_t* __restrict__ offsets,
     total += n;
   }
   const int per = (total + 7) >> 3;
-  const int slot = blockIdx.x >> 3;
-  const int L = (int)(blockIdx.x & 7) * per + slot;
+  const int slot = block >> 3;
+  const int L = (int)(block & 7) * per + slot;
   if (slot >= per || L >= total) return false;  // (uniform)
   const int i = L - (before + inc - cnt);
   if (i >= 0 && i < cnt) {  // one thread: its expert holds tile L
