@@ -22,6 +22,16 @@ namespace {
 
 constexpr int kDlThreads = 256;
 
+// One wave per token, in two grid dimensions (one holds less than 2^32 threads).
+inline dim3 dl_grid(int T) {
+  const unsigned n = ((unsigned)T + 3) / 4, x = n < 1u << 20 ? n : 1u << 20;
+  return dim3(x, (n + x - 1) / x);
+}
+__device__ __forceinline__ unsigned dl_token() {
+  return __builtin_amdgcn_readfirstlane((blockIdx.y * gridDim.x + blockIdx.x) * (kDlThreads / 64) +
+                                        (threadIdx.x >> 6));
+}
+
 // Renormalised gates: dl_slot[t, j] = g_j (dg_j - sum_i g_i dg_i) (0 for
 // unrouted slots).  dl_dense and dlogits (both optional) get the dense [T, E]
 // gradient.  One wave per token: lane j holds slot j (then j + 64, ...), lane e
@@ -31,9 +41,8 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_kernel(
     const float* __restrict__ dgate, const int32_t* __restrict__ idx,
     const float* __restrict__ gate, int T, int E, int k, float* __restrict__ dl_out,
     float* __restrict__ dl_dense, float* __restrict__ dlogits) {
-  const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * (kDlThreads / 64) +
-                                               (int)(threadIdx.x >> 6));
-  if (t >= T) return;
+  const unsigned t = dl_token();
+  if (t >= (unsigned)T) return;
   const int lane = threadIdx.x & 63;
   const size_t s0 = (size_t)t * k;
   auto from_lane = [](float v, int l) {
@@ -85,9 +94,8 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
     const float* __restrict__ gate, const float* __restrict__ logits,
     const uint8_t* __restrict__ alive, int T, int E, int k, float* __restrict__ dl_out,
     float* __restrict__ dlogits) {
-  const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * (kDlThreads / 64) +
-                                               (int)(threadIdx.x >> 6));
-  if (t >= T) return;
+  const unsigned t = dl_token();
+  if (t >= (unsigned)T) return;
   const int lane = threadIdx.x & 63;
   const size_t s0 = (size_t)t * k;
   float s = 0.0f;
@@ -617,7 +625,7 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
                                              align_up((size_t)T_ * k * sizeof(float), 256));
   char* base = reinterpret_cast<char*>(dl_dense) + align_up((size_t)T_ * E * sizeof(float), 256);
   if (!renorm) {
-    hipLaunchKernelGGL(route_bwd_dl_full_kernel, dim3((T_ + 3) / 4), dim3(kDlThreads), 0, s, dgate,
+    hipLaunchKernelGGL(route_bwd_dl_full_kernel, dl_grid(T_), dim3(kDlThreads), 0, s, dgate,
                        idx, gate, logits, alive, T_, E, k, dl_dense, dlogits);
     if (dx)
       hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDx>),
@@ -629,7 +637,7 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
     return hipGetLastError();
   }
   const bool dense = dw_router && renorm_dw_dense(k, E);
-  hipLaunchKernelGGL(route_bwd_dl_kernel, dim3((T_ + 3) / 4), dim3(kDlThreads), 0, s, dgate, idx,
+  hipLaunchKernelGGL(route_bwd_dl_kernel, dl_grid(T_), dim3(kDlThreads), 0, s, dgate, idx,
                      gate, T_, E, k, dl, dense ? dl_dense : nullptr, dlogits);
   if (dx)
     hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,

@@ -32,3 +32,32 @@ def test_f32_ffn_with_capacity_for_2_to_the_23_rows():
     assert (y[n] == 7.0).all()
     del x, y
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("renorm", [True, False])
+def test_router_weight_gradients_of_2_to_the_26_tokens(renorm):
+    T, E, k, d = 1 << 26, 2, 1, 8
+    case(f"router backward, weights only T={T} E={E} d={d} renorm={renorm}")
+    x = torch.zeros((T, d), dtype=torch.bfloat16, device="cuda")
+    idx = torch.zeros((T, k), dtype=torch.int32, device="cuda")
+    gate = torch.ones((T, k), device="cuda")
+    dg = torch.zeros((T, k), device="cuda")
+    logits = torch.zeros((T, E), device="cuda")
+    off = torch.tensor([0, T, T], dtype=torch.int32, device="cuda")
+    src = torch.arange(T, dtype=torch.int32, device="cuda")
+    # the last tokens carry a gradient: full softmax p = 1/2, gate 1/2
+    gate[-3:] = 0.5
+    dg[-3:] = 4.0
+    x[-3:] = 1.0
+    wr = torch.zeros((E, d), dtype=torch.bfloat16, device="cuda")
+    _, dw, db, dl = laep.moe_route_bwd(dg, idx, gate, x, wr, renorm=renorm,
+                                       logits=None if renorm else logits, offsets=off,
+                                       row_src=src, data=False, want_dbias=True,
+                                       want_dlogits=True)
+    torch.cuda.synchronize()
+    # s = g dg = 2; renorm: g (dg - s) = 1; full: p (q - s) = 1 and -1
+    want = [1.0, 0.0] if renorm else [1.0, -1.0]
+    assert dl[-3:].tolist() == [want] * 3 and not dl[:-3].any()
+    assert db.tolist() == [3 * w for w in want]
+    assert dw.tolist() == [[3 * w] * d for w in want]
+    torch.cuda.empty_cache()
