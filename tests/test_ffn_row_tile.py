@@ -34,3 +34,13 @@ def test_row_tile(R, E, d, f, want):
 def test_more_rows_never_take_shorter_tiles(E, d, f):
     heights = [row_tile(int(1.2 ** i), E, d, f) for i in range(80)]
     assert heights == sorted(heights) and heights[0] == 32 and heights[-1] == 256
+
+
+@pytest.mark.parametrize("R,E,d,f", [
+    (32744, 32, 64, 512), (32744, 32, 1024, 64),   # test_ffn_fwd_parity, one-step k-loops
+    (60000, 40, 64, 256),                          # test_ffn_fwd_many_tiles
+    (16000, 16, 512, 512),                         # the two concurrent calls
+])
+def test_sizes_of_the_persistent_kernels_tests(R, E, d, f):
+    """GPU tests written for the 256-row kernels run them."""
+    assert row_tile(R, E, d, f) == 256

@@ -697,13 +697,13 @@ def _heavy_tailed_counts(rng, E, total):
 
 
 @pytest.mark.parametrize("seed,E,total,d,f", [
-    (0, 64, 80000, 128, 64),    # about 380 row tiles: several tiles per persistent workgroup
+    (0, 64, 80000, 128, 64),    # 128-row tiles, as the last; the second 256-row ones
     (1, 40, 60000, 64, 256),
     (2, 16, 40000, 256, 128),
 ])
 def test_ffn_fwd_many_tiles(seed, E, total, d, f):
-    """Uneven expert loads over hundreds of tiles per product, so every
-    persistent workgroup takes several tiles from its XCD's queue."""
+    """Uneven expert loads over hundreds of tiles per product, so that (256-row
+    tiles) every persistent workgroup takes several from its XCD's queue."""
     counts = _heavy_tailed_counts(np.random.default_rng(40 + seed), E, total)
     test_ffn_fwd_parity("bf16", counts, d, f)
 
