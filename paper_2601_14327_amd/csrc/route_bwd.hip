@@ -22,12 +22,13 @@ namespace {
 
 constexpr int kDlThreads = 256;
 
-// One wave per token, in two grid dimensions (one holds less than 2^32 threads).
-inline dim3 dl_grid(int T) {
-  const unsigned n = ((unsigned)T + 3) / 4, x = n < 1u << 20 ? n : 1u << 20;
+// Waves in two grid dimensions (one holds less than 2^32 threads).
+inline dim3 dl_grid(int T, int tokens_per_wave) {
+  const unsigned per = (kDlThreads / 64) * (unsigned)tokens_per_wave;
+  const unsigned n = ((unsigned)T + per - 1) / per, x = n < 1u << 20 ? n : 1u << 20;
   return dim3(x, (n + x - 1) / x);
 }
-__device__ __forceinline__ unsigned dl_token() {
+__device__ __forceinline__ unsigned dl_wave() {
   return __builtin_amdgcn_readfirstlane((blockIdx.y * gridDim.x + blockIdx.x) * (kDlThreads / 64) +
                                         (threadIdx.x >> 6));
 }
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_kernel(
     const float* __restrict__ dgate, const int32_t* __restrict__ idx,
     const float* __restrict__ gate, int T, int E, int k, float* __restrict__ dl_out,
     float* __restrict__ dl_dense, float* __restrict__ dlogits) {
-  const unsigned t = dl_token();
+  const unsigned t = dl_wave();
   if (t >= (unsigned)T) return;
   const int lane = threadIdx.x & 63;
   const size_t s0 = (size_t)t * k;
@@ -84,6 +85,42 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_kernel(
   }
 }
 
+// The same for the slots alone, at most 64: `lanes` lanes per token (the power of
+// two from k up), 64 / lanes tokens per wave.  (A wave per token for one slot took
+// 9 us at 40000 tokens; a thread per token, each reading its slots alone, 7 us at
+// 1000 tokens of 8 slots; here 3 and 3.)
+inline int dl_lanes(int k) {
+  int lanes = 1;
+  while (lanes < k) lanes *= 2;
+  return lanes;
+}
+__global__ __launch_bounds__(kDlThreads) void route_bwd_dl_slots_kernel(
+    const float* __restrict__ dgate, const int32_t* __restrict__ idx,
+    const float* __restrict__ gate, int T, int k, int lanes, float* __restrict__ dl_out) {
+  const int lane = threadIdx.x & 63;
+  const int sub = lane & (lanes - 1), group = lane - sub;
+  const unsigned t = dl_wave() * (64u / lanes) + (unsigned)(lane / lanes);
+  const bool on = t < (unsigned)T && sub < k;
+  const size_t at = (size_t)t * k + sub;
+  int e = -1;
+  float g = 0.0f, dg = 0.0f;
+  if (on) {
+    e = idx[at];
+    g = gate[at];
+    dg = dgate[at];
+  }
+  const float p = e >= 0 ? g * dg : 0.0f;
+  float s = 0.0f;
+  for (int j = 0; j < k; j += 8) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = __shfl(p, group + ((j + u) & (lanes - 1)), kWave);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += j + u < k ? v[u] : 0.0f;
+  }
+  if (on) dl_out[at] = e >= 0 ? g * (dg - s) : 0.0f;
+}
+
 // Full-softmax gates: dl_full[t, e] = p_e (q_e - sum_j g_j dg_j) over alive e,
 // p = softmax of the alive logits, q_e = dg_j at e = idx[t, j].  One wave per
 // token, lane l owning experts l, l + 64, ...: the logits are read and dl
@@ -94,7 +131,7 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
     const float* __restrict__ gate, const float* __restrict__ logits,
     const uint8_t* __restrict__ alive, int T, int E, int k, float* __restrict__ dl_out,
     float* __restrict__ dlogits) {
-  const unsigned t = dl_token();
+  const unsigned t = dl_wave();
   if (t >= (unsigned)T) return;
   const int lane = threadIdx.x & 63;
   const size_t s0 = (size_t)t * k;
@@ -625,7 +662,7 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
                                              align_up((size_t)T_ * k * sizeof(float), 256));
   char* base = reinterpret_cast<char*>(dl_dense) + align_up((size_t)T_ * E * sizeof(float), 256);
   if (!renorm) {
-    hipLaunchKernelGGL(route_bwd_dl_full_kernel, dl_grid(T_), dim3(kDlThreads), 0, s, dgate,
+    hipLaunchKernelGGL(route_bwd_dl_full_kernel, dl_grid(T_, 1), dim3(kDlThreads), 0, s, dgate,
                        idx, gate, logits, alive, T_, E, k, dl_dense, dlogits);
     if (dx)
       hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDx>),
@@ -637,8 +674,14 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
     return hipGetLastError();
   }
   const bool dense = dw_router && renorm_dw_dense(k, E);
-  hipLaunchKernelGGL(route_bwd_dl_kernel, dl_grid(T_), dim3(kDlThreads), 0, s, dgate, idx,
-                     gate, T_, E, k, dl, dense ? dl_dense : nullptr, dlogits);
+  if (!dense && !dlogits && k <= 64) {
+    const int lanes = dl_lanes(k);
+    hipLaunchKernelGGL(route_bwd_dl_slots_kernel, dl_grid(T_, 64 / lanes), dim3(kDlThreads), 0, s,
+                       dgate, idx, gate, T_, k, lanes, dl);
+  } else {
+    hipLaunchKernelGGL(route_bwd_dl_kernel, dl_grid(T_, 1), dim3(kDlThreads), 0, s, dgate, idx,
+                       gate, T_, E, k, dl, dense ? dl_dense : nullptr, dlogits);
+  }
   if (dx)
     hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,
                        w_router, idx, dl, T_, k, d, accumulate_dx, dx);

@@ -53,6 +53,26 @@ def test_weights(T, E, k, d, dtype):
     assert ((db.double() - full.sum(0)).abs() <= TOL_F32 * full.abs().sum(0) + 1e-30).all()
 
 
+@pytest.mark.parametrize("T,k", [(1, 1), (300, 1), (65, 2), (1000, 3), (33, 8), (257, 13),
+                                 (70, 64), (40, 65)])
+def test_slots_alone(T, k):
+    """Without the dense rows (several tokens share a wave, up to 64 slots) the
+    slots' gradients, seen through dx, keep their bits; unrouted slots among them."""
+    E, d = 128, 64
+    case(f"router renorm slots T={T} k={k}")
+    x, wr, idx, gate, _, _, dg = _inputs(T, E, k, d, torch.float32, 7 * T + k)
+    if k > 2:
+        idx[T // 2, k - 2:], gate[T // 2, k - 2:] = -1, 0.0
+        dg[T // 2, k - 1] = float("nan")   # not read
+    _, off, _, src = laep.moe_expert_counts(idx, E, want_row_src=True)
+    kw = dict(offsets=off, row_src=src, weights=False)
+    a = laep.moe_route_bwd(dg, idx, gate, x, wr, **kw)[0]
+    b, _, _, dl = laep.moe_route_bwd(dg, idx, gate, x, wr, want_dlogits=True, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(a, b)
+    assert rownorm_err(host(a), host(dl.double() @ wr.double())) <= TOL_F32
+
+
 @pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
 @pytest.mark.parametrize("E,k", [(64, 4), (130, 4),
                                  (64, 1), (130, 1)])   # one slot: dl is 0, and 0 * inf NaN
