@@ -607,12 +607,25 @@ inline int seg_max(int T, int k, int E) { return (int)(((int64_t)T * k + kSegRow
 
 // Renormalised gates, dW_r: the dense product over all tokens and experts (dl is
 // zero outside the k selected ones) or the segment sums over the routed rows.  The
-// dense product's work grows with E in steps of its 64-expert tiles, the segments'
-// reads with k.  Whole weights-only call, dense / segments, d 2048, 8192 tokens:
-// 64 experts top-8 42 / 74 us, top-2 40 / 58, 16 experts top-2 33 / 60; 128 experts
-// top-8 64 / 72, top-2 64 / 58; 256 experts top-8 110 / 71, top-2 111 / 47.  1000
-// tokens of 64 experts, top-2, d 1024: 14 / 20.
-inline bool renorm_dw_dense(int k, int E) { return E <= 64 || E <= 16 * k; }
+// dense product multiplies a token's x by 64 experts at a time and reads it as
+// often, the segments read it k times, but gather it and, with few rows an expert,
+// wait for their loads more than they use them.  So: dense from 8 slots per 64
+// experts, and for less than that while x is small; the line grows with k, and
+// steeply, since with one slot the segments read x once, in order.  Whole
+// weights-only call, dense / segments, us, bf16, d 2048 (x of 33.6 MB at 8192
+// tokens):
+//             experts, slots   8, 1       64, 1      64, 2      64, 8      128, 8
+//     1000 tokens            15 / 38    16 / 17    16 / 20    16 / 40    23 / 28
+//     8192 tokens            30 / 56    34 / 55    37 / 58    38 / 69    60 / 67
+//    40000 tokens           115 / 76   118 / 64   126 / 71   130 / 202  227 / 197
+// Over 1863 sizes (64 to 100000 tokens, d 256 to 4096, 4 to 256 experts, both
+// types) eight are more than 3 % behind the segments, 22 % and 4 us at most.
+inline bool renorm_dw_dense(int T, int E, int k, int d, int elem_bytes) {
+  const int tiles = (E + kDenseBM - 1) / kDenseBM;
+  const double bytes = (double)T * d * elem_bytes;
+  if (k >= 8 * tiles) return true;
+  return tiles == 1 ? bytes <= 12e6 * k * k : E <= 16 * k && bytes <= 16e6;
+}
 
 size_t route_bwd_ws_bytes(int T, int k, int E, int d) {
   const int m = seg_max(T, k, E);
@@ -673,7 +686,7 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
     if (dw_router) launch_dense_dw<T, false>(dl_dense, x, T_, E, d, base, dw_router, dbias, idx, k, s);
     return hipGetLastError();
   }
-  const bool dense = dw_router && renorm_dw_dense(k, E);
+  const bool dense = dw_router && renorm_dw_dense(T_, E, k, d, (int)sizeof(T));
   if (!dense && !dlogits && k <= 64) {
     const int lanes = dl_lanes(k);
     hipLaunchKernelGGL(route_bwd_dl_slots_kernel, dl_grid(T_, 64 / lanes), dim3(kDlThreads), 0, s,

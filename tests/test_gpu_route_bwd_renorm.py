@@ -1,6 +1,6 @@
 """The router's weight gradients of renormalised gates, dense product and
-segment sums (the choice falls between E = 64 or 16 k and more), against plain
-float64, at the edges of their tiles; an infinite token touches only the rows of
+segment sums (the choice falls at 8 slots per 64 experts and at sizes of x),
+against plain float64, at the edges of their tiles; an infinite token touches only the rows of
 the experts it is routed to."""
 import numpy as np
 import pytest
@@ -50,6 +50,27 @@ def test_weights(T, E, k, d, dtype):
     cond = (full.abs().t() @ x.double().abs()).clamp_min(1e-30)
     assert ((dw.double() - full.t() @ x.double()).abs() <= TOL_F32 * cond).all()
     assert rownorm_err(host(dl), host(full)) <= TOL_F32
+    assert ((db.double() - full.sum(0)).abs() <= TOL_F32 * full.abs().sum(0) + 1e-30).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("T,E,k,d", [
+    (24000, 64, 2, 1024),   # segments for x of 49 MB and more
+    (5900, 64, 1, 1024),    # bf16 12.1 MB: segments, 11.9 MB: dense
+    (5800, 64, 1, 1024),
+])
+def test_weights_past_the_size_of_x(T, E, k, d, dtype):
+    """Against float64 on the call's own logit gradients."""
+    case(f"router renorm weights by size T={T} E={E} k={k} d={d} {dtype}")
+    a = _inputs(T, E, k, d, dtype, T)
+    if k == 1:   # (its gradient is 0: other gates than the softmax's)
+        a[3].copy_(torch.rand((T, k), device="cuda") + 0.05)
+    dw, db, dl = _dw(*a)
+    full, x = dl.double(), a[0].double()
+    # fp32 sums of 128 rows (segments) or up to 768 tokens (splits, most of them 0),
+    # then of their partial sums: about 160 roundings of 6e-8
+    cond = (full.abs().t() @ x.abs()).clamp_min(1e-30)
+    assert ((dw.double() - full.t() @ x).abs() <= TOL_F32 * cond).all()
     assert ((db.double() - full.sum(0)).abs() <= TOL_F32 * full.abs().sum(0) + 1e-30).all()
 
 
