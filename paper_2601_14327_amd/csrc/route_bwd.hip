@@ -177,10 +177,10 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
   }
 }
 
-// Renormalised gates: dx[t] (+)= sum over slots of w * W_r[row], row ids from
-// `ids` ([T, slots], -1 = none), weights dl [T, slots].  One wave per token (its
-// ids and weights are wave-uniform loads); each lane owns the 8-column vectors
-// lane, lane + 64, ...
+// dx[t] (+)= sum over slots of w * W_r[row], row ids from `ids` ([T, slots], -1 =
+// none) or the slot itself (ids == NULL: full-softmax gates of few experts),
+// weights dl [T, slots].  One wave per token (its ids and weights are wave-uniform
+// loads); each lane owns the 8-column vectors lane, lane + 64, ...
 template <typename T>
 __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
     const T* __restrict__ w_router, const int32_t* __restrict__ ids,
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256) void route_bwd_dx_kernel(
         r[u] = -1;
         w[u] = 0.0f;
         if (s < slots) {
-          r[u] = ids[o + s];
+          r[u] = ids ? ids[o + s] : s;
           w[u] = dl[o + s];
         }
         if (w[u] == 0.0f) r[u] = -1;
@@ -627,6 +627,13 @@ inline bool renorm_dw_dense(int T, int E, int k, int d, int elem_bytes) {
   return tiles == 1 ? bytes <= 12e6 * k * k : E <= 16 * k && bytes <= 16e6;
 }
 
+// dx of full-softmax gates: over few experts the dense product's tiles hold little
+// work beside their rows of dx, which a wave per token reads and writes in whole
+// lines; with few tokens that is one long wait.  By rows / dense, us, accumulated,
+// bf16: 8192 tokens, d 2048, 4 experts 25 / 47, 8 31 / 47, 16 48 / 47, 32 80 / 47;
+// 40000 tokens 90 / 139, 116 / 140, 184 / 143; 1000 tokens of 8 experts 15 / 12.
+inline bool dx_by_rows(int T, int E) { return E <= 8 && T >= 400 * E && T < 1 << 26; }
+
 size_t route_bwd_ws_bytes(int T, int k, int E, int d) {
   const int m = seg_max(T, k, E);
   const size_t seg = table_bytes(m) + align_up((size_t)m * d * sizeof(float), 256) +
@@ -677,7 +684,11 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
   if (!renorm) {
     hipLaunchKernelGGL(route_bwd_dl_full_kernel, dl_grid(T_, 1), dim3(kDlThreads), 0, s, dgate,
                        idx, gate, logits, alive, T_, E, k, dl_dense, dlogits);
-    if (dx)
+    if (dx && dx_by_rows(T_, E))
+      hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,
+                         w_router, static_cast<const int32_t*>(nullptr), dl_dense, T_, E, d,
+                         accumulate_dx, dx);
+    else if (dx)
       hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDx>),
                          dim3((unsigned)((T_ + kDenseBM - 1) / kDenseBM),
                               (unsigned)((d + kDenseBN - 1) / kDenseBN)),

@@ -21,6 +21,10 @@ TD = {"bf16": torch.bfloat16, "f32": torch.float32}
     (129, 72, 45, 8, "bf16", 5),       # E odd: unaligned dl rows
     (2500, 264, 256, 8, "bf16", 0),    # several splits, the last one short
     (1000, 1024, 33, 2, "f32", 1),
+    (3200, 72, 8, 2, "bf16", 1),       # dx by rows: 8 experts, 400 tokens each
+    (3199, 72, 8, 2, "bf16", 1),       # and dense
+    (3700, 136, 9, 2, "f32", 0),
+    (900, 136, 2, 1, "f32", 1),        # by rows, one expert left
 ])
 def test_dense_route_bwd(T, d, E, k, dtype, dead):
     td = TD[dtype]
