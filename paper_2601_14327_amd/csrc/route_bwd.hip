@@ -125,21 +125,33 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_slots_kernel(
 // p = softmax of the alive logits, q_e = dg_j at e = idx[t, j].  One wave per
 // token, lane l owning experts l, l + 64, ...: the logits are read and dl
 // written in whole lines (one thread per token walked its row alone, every
-// load touching 64 lines: 103 us at 4096 tokens over 128 experts).
+// load touching 64 lines: 103 us at 4096 tokens over 128 experts).  PACKED: up to
+// 32 experts, `lanes` lanes per token (the power of two from E up), 64 / lanes
+// tokens per wave, lane e its expert e (a wave per token took 14 us at 40000
+// tokens, now 5).
+template <bool PACKED>
 __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
     const float* __restrict__ dgate, const int32_t* __restrict__ idx,
     const float* __restrict__ gate, const float* __restrict__ logits,
-    const uint8_t* __restrict__ alive, int T, int E, int k, float* __restrict__ dl_out,
-    float* __restrict__ dlogits) {
-  const unsigned t = dl_wave();
-  if (t >= (unsigned)T) return;
-  const int lane = threadIdx.x & 63;
+    const uint8_t* __restrict__ alive, int T, int E, int k, int lanes,
+    float* __restrict__ dl_out, float* __restrict__ dlogits) {
+  const int in_wave = threadIdx.x & 63;
+  const unsigned t = PACKED ? dl_wave() * (64u / lanes) + (unsigned)(in_wave / lanes) : dl_wave();
+  if (t >= (unsigned)T) return;  // (whole groups)
+  const int lane = PACKED ? in_wave & (lanes - 1) : in_wave;
+  const int width = PACKED ? lanes : 64;
+  auto sum = [&](float v) {  // over the token's lanes
+#pragma unroll
+    for (int off = PACKED ? 16 : 32; off >= 1; off >>= 1)
+      if (off < width) v += __shfl_xor(v, off, kWave);
+    return v;
+  };
   const size_t s0 = (size_t)t * k;
   float s = 0.0f;
-  for (int j = lane; j < k; j += 64)
+  for (int j = lane; j < k; j += width)
     if (idx[s0 + j] >= 0) s += gate[s0 + j] * dgate[s0 + j];
-  s = wave_sum(s);
-  constexpr int EPL = 4;  // at most 256 experts
+  s = sum(s);
+  constexpr int EPL = PACKED ? 1 : 4;  // at most 256 experts
   float l[EPL], q[EPL];
   bool a[EPL];
   float m = -INFINITY;
@@ -152,8 +164,9 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
     m = fmaxf(m, l[u]);
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-  for (int j = 0; j < k; ++j) {  // (uniform loads)
+  for (int off = PACKED ? 16 : 32; off >= 1; off >>= 1)
+    if (off < width) m = fmaxf(m, __shfl_xor(m, off, kWave));
+  for (int j = 0; j < k; ++j) {  // (one address per token)
     const int ej = idx[s0 + j];
     const float dg = dgate[s0 + j];
 #pragma unroll
@@ -165,7 +178,7 @@ __global__ __launch_bounds__(kDlThreads) void route_bwd_dl_full_kernel(
     l[u] = a[u] ? __expf(l[u] - m) : 0.0f;
     z += l[u];
   }
-  z = wave_sum(z);
+  z = sum(z);
   const float inv = z > 0.0f ? 1.0f / z : 0.0f;
 #pragma unroll
   for (int u = 0; u < EPL; ++u) {
@@ -682,8 +695,10 @@ hipError_t launch_route_bwd_t(const float* dgate, const int32_t* idx, const floa
                                              align_up((size_t)T_ * k * sizeof(float), 256));
   char* base = reinterpret_cast<char*>(dl_dense) + align_up((size_t)T_ * E * sizeof(float), 256);
   if (!renorm) {
-    hipLaunchKernelGGL(route_bwd_dl_full_kernel, dl_grid(T_, 1), dim3(kDlThreads), 0, s, dgate,
-                       idx, gate, logits, alive, T_, E, k, dl_dense, dlogits);
+    const int lanes = E <= 32 ? dl_lanes(E) : 64;
+    const auto dl_full = lanes < 64 ? route_bwd_dl_full_kernel<true> : route_bwd_dl_full_kernel<false>;
+    hipLaunchKernelGGL(dl_full, dl_grid(T_, 64 / lanes), dim3(kDlThreads), 0, s, dgate, idx, gate,
+                       logits, alive, T_, E, k, lanes, dl_dense, dlogits);
     if (dx && dx_by_rows(T_, E))
       hipLaunchKernelGGL(route_bwd_dx_kernel<T>, dim3((unsigned)((T_ + 3) / 4)), dim3(256), 0, s,
                          w_router, static_cast<const int32_t*>(nullptr), dl_dense, T_, E, d,

@@ -25,6 +25,9 @@ TD = {"bf16": torch.bfloat16, "f32": torch.float32}
     (3199, 72, 8, 2, "bf16", 1),       # and dense
     (3700, 136, 9, 2, "f32", 0),
     (900, 136, 2, 1, "f32", 1),        # by rows, one expert left
+    (257, 64, 32, 8, "bf16", 3),       # 32, 20 (of 32) and 3 (of 4) lanes a token
+    (501, 64, 20, 20, "f32", 2),
+    (101, 64, 3, 1, "f32", 0),
 ])
 def test_dense_route_bwd(T, d, E, k, dtype, dead):
     td = TD[dtype]
