@@ -671,13 +671,16 @@ template <typename T, bool SPARSE>
 void launch_dense_dw(const float* dl, const T* x, int T_, int E, int d, char* base,
                      float* dw_router, float* dbias, const int32_t* idx, int k, hipStream_t s) {
   const DenseSplit sp = dense_split(T_, E, d);
-  float* part = reinterpret_cast<float*>(base);
-  float* part_b = reinterpret_cast<float*>(base + align_up((size_t)sp.n * E * d * sizeof(float), 256));
+  const bool one = sp.n == 1;  // its partial tiles are dW_r
+  float* part = one ? dw_router : reinterpret_cast<float*>(base);
+  float* part_b = one ? dbias : reinterpret_cast<float*>(
+                                    base + align_up((size_t)sp.n * E * d * sizeof(float), 256));
   hipLaunchKernelGGL((route_bwd_dense_kernel<T, kDw, SPARSE>),
                      dim3((unsigned)((E + kDenseBM - 1) / kDenseBM),
                           (unsigned)((d + kDenseBN - 1) / kDenseBN), (unsigned)sp.n),
                      dim3(256), 0, s, dl, x, nullptr, E, T_, sp.per, E, d, 0,
                      static_cast<T*>(nullptr), part, dbias ? part_b : nullptr, idx, k);
+  if (one) return;
   const size_t n = (size_t)E * d;  // >= E
   hipLaunchKernelGGL(route_bwd_dense_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256),
                      0, s, part, part_b, sp.n, E, d, dw_router, dbias);
