@@ -26,7 +26,8 @@ __device__ __forceinline__ bool marked(const long long* loads, int E, int e, dou
 #pragma unroll 8
   for (int j = 0; j < E; ++j) {
     const long long cj = loads[j];
-    running += (cj < c || (cj == c && j <= e)) ? cj : 0ll;
+    // (bitwise: a select, where || and && branch around every load of the loop)
+    running += ((int)(cj < c) | ((int)(cj == c) & (int)(j <= e))) ? cj : 0ll;
   }
   return (double)running < beta_thr && (double)c < alpha_thr;
 }
@@ -142,7 +143,8 @@ __global__ __launch_bounds__(kWindowThreads) void expert_pruning_kernel(
     for (int j = 0; j < E; ++j) {
       const int mj = s_mark[j];
       const long long sj = s_sum[j];
-      rank += (mj > m) || (mj == m && (sj < sm || (sj == sm && j < tid)));
+      rank += (int)(mj > m) |
+              ((int)(mj == m) & ((int)(sj < sm) | ((int)(sj == sm) & (int)(j < tid))));
     }
     alive[(size_t)layer * E + tid] = rank < n_dis ? 0 : 1;
     if (marker_out) marker_out[(size_t)layer * E + tid] = m;
