@@ -335,12 +335,12 @@ int moe_permute(const void* x, int dtype, const int32_t* dest_row, int T,
  *   Constraints: d_model % 64 == 0, d_ff % 64 == 0, R < 2^31; bf16: one
  *   expert's w_gate_up under 2 GiB (4*d_ff*d_model bytes), since the GEMMs
  *   address it with 32-bit offsets (LAEP_ERR_UNSUPPORTED otherwise).
- *   LAEP_BF16 runs on the bf16 matrix cores (fp32 accumulation).  LAEP_F32
- *   is a plain fp32 FMA loop (no matrix cores), meant for small parity
- *   layers, not for speed; its backward is not implemented.
+ *   LAEP_BF16 runs on the bf16 matrix cores (fp32 accumulation), LAEP_F32 on
+ *   the fp32 ones (fp32 products and sums), in 32-row tiles meant for small
+ *   layers; its backward is not implemented.
  *   Workspace: moe_workspace_bytes(LAEP_CALL_FFN_FWD, R, 1, E, d_model, d_ff)
- *   (holds H, the tile tables and the products' tile counters, which the
- *   call's first kernel resets; on return H [R, d_ff] (dtype) is at byte
+ *   (holds H and, for bf16 calls of 256-row tiles, the tile lists and the
+ *   products' tile counters, which the call's first kernel resets; on return H [R, d_ff] (dtype) is at byte
  *   offset 0, which moe_grouped_ffn_bwd can take as h_fwd).
  */
 int moe_grouped_ffn_fwd(const void* x_perm, const void* w_gate_up,

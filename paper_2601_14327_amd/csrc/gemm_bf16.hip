@@ -182,8 +182,10 @@ __device__ __forceinline__ void store_down(const GemmParams& p, const TileEntry&
 // ---------------------------------------------------------------------------
 // Persistent kernel: one workgroup per CU walks its XCD's contiguous tile range,
 // taking tiles from a per-XCD counter (so uneven tiles balance as the hardware
-// dispatcher would, without a workgroup launch per tile).  Main loop: 256 x 256
-// tiles, 8 waves (2 x 4, each 128 x 64), k-steps of 64 through a ring of five 32 KB
+// dispatcher would, without a workgroup launch per tile; the counter's address is
+// uniform, so the compiler adds once per wave and reads the reply at once: wave 0 waits
+// for it, and for all that it has in flight, at the start of each k-loop).  Main loop:
+// 256 x 256 tiles, 8 waves (2 x 4, each 128 x 64), k-steps of 64 in a ring of five 32 KB
 // halves.  When a tile's k-loop ends, half of its rows are stored while the next
 // tile's entry and gathered row ids load, then the next tile's first four halves are
 // issued into the free ring, then the other half is stored: the operands' latency
@@ -314,8 +316,8 @@ __global__ __launch_bounds__(64 * NWM * NWN) void gemm_nt_persist_kernel(GemmPar
 
   // The k-loop of one tile, its halves 0 .. 3 already issued, for a wave
   // whose first TMV 32-row blocks hold rows of the expert.  Thread 0 takes
-  // the next tile from the counter at its start (the reply is read after the
-  // loop; the loop's in-order waits only grow stricter for an older load).
+  // the next tile from the counter at its start; the reply is used after the
+  // loop, but waited for here (all of wave 0's loads and stores with it).
   int next_raw = 0;
   auto main_loop = [&](auto tmv_tag) {
     constexpr int TMV = decltype(tmv_tag)::value;
@@ -511,8 +513,7 @@ size_t ffn_fwd_ws_bytes(int64_t R, int E, int d, int f, int dtype) {
     return align_up((size_t)R * f * 2, 256) +
            table_bytes(fwd_list_max(R, E, ceil_div(f, kFwdBN / 2))) +
            table_bytes(fwd_list_max(R, E, ceil_div(d, kFwdBN)));
-  // fp32: H, then one entry per 64-row tile
-  return align_up((size_t)R * f * 4, 256) + table_bytes(ceil_div(R, 64) + E);
+  return align_up((size_t)R * f * 4, 256);  // fp32: H
 }
 
 namespace {
@@ -551,8 +552,6 @@ hipError_t launch_ffn_fwd_products(const void* x_perm, const void* w_gu, const v
   g.strideB = (long long)2 * f * d;
   g.N = 2 * f;
   g.K = d;
-  g.n_tiles_n = nt_gu;
-  g.tiles_per_entry = 1;
   g.out = H;
   g.ldo = f;
   g.out2 = static_cast<bf16_t*>(act_save);
@@ -572,8 +571,6 @@ hipError_t launch_ffn_fwd_products(const void* x_perm, const void* w_gu, const v
   g.strideB = (long long)d * f;
   g.N = d;
   g.K = f;
-  g.n_tiles_n = nt_d;
-  g.tiles_per_entry = 1;
   g.out = static_cast<bf16_t*>(y_perm);
   g.ldo = d;
   g.out2 = nullptr;

@@ -27,7 +27,6 @@ struct GemmParams {
   bf16_t* out;
   long long ldo;
   bf16_t* out2;
-  const bf16_t* aux;
   float* wout;
   long long strideW;
   int accumulate;
@@ -60,19 +59,6 @@ struct GemmParams {
 // column blocks in flight).
 constexpr int kFwdTileGroup = 4;
 constexpr int kBwdTileGroup = 8;
-
-__device__ __forceinline__ void store_bf16x4(bf16_t* p, float a, float b, float c, float d) {
-  u32x2_t w = {pack_bf16x2(a, b), pack_bf16x2(c, d)};
-  *reinterpret_cast<u32x2_t*>(p) = w;
-}
-
-__device__ __forceinline__ void load_bf16x4(const bf16_t* p, float v[4]) {
-  const u32x2_t w = *reinterpret_cast<const u32x2_t*>(p);
-  v[0] = lo_bf16(w[0]);
-  v[1] = hi_bf16(w[0]);
-  v[2] = lo_bf16(w[1]);
-  v[3] = hi_bf16(w[1]);
-}
 
 // 128-byte LDS rows (64 k of bf16, 8 chunks of 16 bytes): chunk c of row r
 // at c ^ ((r ^ r >> 3) & 7), measured free of bank conflicts for the

@@ -305,7 +305,7 @@ hipError_t launch_small_pair(SmallParams g, SmallParams dn, int64_t R, bool gath
 //    8192   80 / 115 /  86 /  77    81 / 121 /  92 /  91     63 / 112 /  83 /  70
 // Over 13 widths (d 64-4096, d_ff 64-2048), 1-256 experts, 8-100000 rows and
 // five kinds of load the rule's choice is at most 10 % behind the 256-row
-// kernels (never behind the ones that staged their output), and takes 0.67 of
+// kernels (not behind the ones that staged their output), and takes 0.67 of
 // their time on average.
 int ffn_fwd_row_tile(int64_t R, int E, int d, int f) {
   // k-steps of one row tile over both products, two more for a tile's two ends;

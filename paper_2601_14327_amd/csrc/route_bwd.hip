@@ -516,7 +516,6 @@ __global__ __launch_bounds__(256) void route_bwd_dw_seg_kernel(
     float* __restrict__ part, float* __restrict__ part_b) {
   __shared__ int s_tok[kSegRows];
   __shared__ float s_w[kSegRows];
-  __shared__ float s_red[4];
   const int entry = blockIdx.x;
   if (entry >= *n_entries) return;
   const TileEntry te = table[entry];
