@@ -31,14 +31,14 @@ template <bool GU>
 __global__ __launch_bounds__(kF32Threads) void gemm_f32_kernel(
     const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb,
     long long strideB, int K, int f, const int32_t* __restrict__ offsets,
-    const int32_t* __restrict__ expert_map, int E, int n_tiles_n, float* __restrict__ out, int ldo,
-    float* __restrict__ out2) {
+    const int32_t* __restrict__ expert_map, int E, int n_tiles_n, unsigned grid_x,
+    float* __restrict__ out, int ldo, float* __restrict__ out2) {
   constexpr int NB = GU ? 2 : 1;   // column blocks of a tile: gate and up, or one
   constexpr int U = GU ? 4 : 8;    // 8-k steps in flight
   constexpr int LD = kT + 4;       // floats per staged row
   __shared__ __attribute__((aligned(16))) float s_part[kF32Waves * NB * kT * LD];
   FoundTile te;
-  if (!find_tile(blockIdx.y * gridDim.x + blockIdx.x, offsets, expert_map, E, kT, n_tiles_n,
+  if (!find_tile(blockIdx.y * grid_x + blockIdx.x, offsets, expert_map, E, kT, n_tiles_n,
                  reinterpret_cast<char*>(s_part), te))
     return;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -139,13 +139,14 @@ hipError_t launch_ffn_fwd_f32(const void* x_perm, const void* w_gu, const void* 
     return dim3((unsigned)x, (unsigned)((blocks + x - 1) / x));
   };
   const int nt_gu = f / kT, nt_d = d / kT;
-  hipLaunchKernelGGL((gemm_f32_kernel<true>), grid(nt_gu), dim3(kF32Threads), 0, s,
+  const dim3 gu = grid(nt_gu), dn = grid(nt_d);
+  hipLaunchKernelGGL((gemm_f32_kernel<true>), gu, dim3(kF32Threads), 0, s,
                      static_cast<const float*>(x_perm), d, static_cast<const float*>(w_gu), d,
-                     (long long)2 * f * d, d, f, offsets, expert_map, E, nt_gu, H, f,
+                     (long long)2 * f * d, d, f, offsets, expert_map, E, nt_gu, gu.x, H, f,
                      static_cast<float*>(act_save));
-  hipLaunchKernelGGL((gemm_f32_kernel<false>), grid(nt_d), dim3(kF32Threads), 0, s, H, f,
+  hipLaunchKernelGGL((gemm_f32_kernel<false>), dn, dim3(kF32Threads), 0, s, H, f,
                      static_cast<const float*>(w_d), f, (long long)d * f, f, f, offsets,
-                     expert_map, E, nt_d, static_cast<float*>(y_perm), d, nullptr);
+                     expert_map, E, nt_d, dn.x, static_cast<float*>(y_perm), d, nullptr);
   return hipGetLastError();
 }
 
