@@ -39,7 +39,7 @@
 // the boundary / as it is (the last with dY written once): 8192 tokens top-8,
 // d 2048, d_ff 1024, 3242 / 3027 / 2935; 32768 rows, 16 experts, d 4096, d_ff 2048,
 // 5531 / 5072 / 4945; 1000 tokens top-2, d 1024, d_ff 2048, 796 / 680 / 680.  The
-// call that forms dY on load: 2165 -> 1969 at the first.
+// call that forms dY on load: 2165 -> 1979 at the first.
 //
 // Gathered X (the dispatch folded into the weight gradient): dW_gu = dA^T X
 // can read X's routed row r straight from token row row_src[r] / k of x, so
