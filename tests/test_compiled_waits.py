@@ -9,7 +9,8 @@ import pytest
 
 from paper_2601_14327_amd import build
 
-DW_D_ON_LOAD = "gemm_bwd_kernelILi256ELi256ELi2ELi4ELi3ELb1ELb0ELb1E"  # dW_d, dY formed on load
+WGRAD = "gemm_bwd_kernelILi256ELi256ELi2ELi4ELi3ELb1E"
+DW_GIVEN, DW_GATHERED, DW_D_ON_LOAD = WGRAD + "Lb0ELb0E", WGRAD + "Lb1ELb0E", WGRAD + "Lb0ELb1E"
 
 
 @pytest.fixture(scope="module")
@@ -27,15 +28,15 @@ def _body(asm, name):
     return [l.split(";")[0].strip() for l in asm[start:end]]
 
 
-def test_on_load_chunks_are_read_after_their_copies(asm):
-    """dW_d with dY formed on load: a thread scales its own copied chunks in
-    place, ds_read_b128 (the fragments are read by ds_read_b64_tr).  Of the 16
-    copies before the loop (A and B of step 0, A and B of step 1, four each) the
-    first twelve have landed at the loop's first such read, all at its first
-    barrier."""
-    body = _body(asm, DW_D_ON_LOAD)
+@pytest.mark.parametrize("kernel", [DW_GIVEN, DW_GATHERED, DW_D_ON_LOAD])
+def test_weight_gradient_halves_land_before_their_barrier(asm, kernel):
+    """Of the 16 copies before the loop (A and B of step 0, A and B of step 1, four
+    each) the first eight have landed at the barrier ahead of the loop, all at the
+    loop's first.  dW_d with dY formed on load also scales each thread's own copied
+    chunks in place, read by ds_read_b128 (fragments by ds_read_b64_tr): those of
+    step 0 ahead of the loop, those of step 1 in its first iteration."""
     flight, copies, reads, barriers = [], 0, 0, 0
-    for l in body:
+    for l in _body(asm, kernel):
         wait = re.match(r"s_waitcnt .*?vmcnt\((\d+)\)", l)
         if wait:
             flight = flight[max(0, len(flight) - int(wait[1])):]
@@ -45,11 +46,12 @@ def test_on_load_chunks_are_read_after_their_copies(asm):
             copies += copy
         elif l.startswith("ds_read_b128"):
             reads += 1
-            landed = 4 if reads <= 4 else 12   # step 0's own chunks, then step 1's
+            landed = 4 if reads <= 4 else 12
             assert not [c for c in flight if c is not None and c < landed], (reads, flight)
         elif l == "s_barrier":
             barriers += 1
             assert not [c for c in flight if c is not None and c < (8 if barriers == 1 else 16)]
             if barriers == 2:
                 break
-    assert copies == 20 and reads == 8 and barriers == 2   # (A of step 2 in the loop)
+    assert copies == 20 and barriers == 2   # (A of step 2 in the loop)
+    assert reads == (8 if kernel == DW_D_ON_LOAD else 0)
